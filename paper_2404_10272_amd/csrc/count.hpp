@@ -1,8 +1,8 @@
 // The counting pass of the sampler: one ray per lane walks the grid, counts
 // its lattice samples, keeps its occupied runs and adds its count to the scan
 // tile and expansion chunk sums.  Shared by the sampler's two sources: the
-// Alg. 2 walks over a tree are instantiated in count_skip.hip, built at a
-// different optimisation level; the rest in sample.hip.
+// Alg. 2 walks over a tree are instantiated in count_skip.hip, the rest in
+// sample.hip.
 #pragma once
 #pragma clang fp contract(off)
 
@@ -61,16 +61,20 @@ __device__ __forceinline__ void add_chunk_sums(int64_t ray, int32_t n, int64_t *
 // counts[i] = samples of ray i; nruns[i] = its occupied runs (kRunsLost: the
 // run pool ran dry, the traversal fill writes the ray); the runs themselves
 // go to the pool's slots and chunks; tile_sums[k] gains the counts of rays
-// k*kScanTile .. (k+1)*kScanTile-1.  Single-level walks of the Alg. 1 loop
-// ask for 7 waves per SIMD (8 for the dense march): the prioritised long
-// waves then share their SIMD with more short ones (the compiler would
-// otherwise settle at 6 once the span is computed before the walk).  So do
-// the single-level Alg. 2 walks over a tree, which count_skip.hip builds at
-// -O2 (at -O1 their nested loops took 14-40% longer).  The single-level
-// Alg. 2 chessboard walk asks for 5 (83 VGPRs, no spills).  The cascade walks of
-// the Alg. 1 loop over the dense grid, the hierarchical and the sub-leaf
-// steps ask for 5 (70 to 87 VGPRs at -O1, no spills; the compiler would
-// settle at 4).
+// k*kScanTile .. (k+1)*kScanTile-1.
+//
+// Bound by VALU issue while the chip is full: an 800x800 view of a 128^3 grid
+// issues 56.6 M wave instructions walking the tree (87.0 M on the bitfield),
+// 92 (141) us at one per four clocks and SIMD, of 113-128 (133) us measured,
+// with 85% of the lanes active.  The steps compute all three axes' crossings
+// and select instead of branching per axis; with branches the same walks took
+// 142-156 (166-172) us at 64% of the lanes, the four-cascade one 310 us
+// against 272, the chessboard one 99 against 64.
+//
+// Occupancy asked for (waves per SIMD): single-level walks of the Alg. 1 loop
+// 7 (8 on the bitfield, whose walk needs 60 VGPRs): the tree walk took
+// 139 / 132 / 128 / 135 us at 5 / 6 / 7 / 8.  Cascade walks 5: 272 us against
+// 300 at 3, 4 and 6, where they have too few waves or spill in the loop.
 constexpr int count_waves_per_eu(int kGrid, bool kSkip, bool kL1) {
     return kL1 ? (kGrid == 0 ? 8 : kSkip && kGrid == 2 ? 5 : 7)
                : (!kSkip && (kGrid == 0 || kGrid == 1 || kGrid == 4) ? 5 : 1);
@@ -100,14 +104,14 @@ count_kernel(GridView g, const float *__restrict__ origins, const float *__restr
             load_ray(origins, dirs, i, o, d);
             s = l1_span(g, o, d, lat);
         }
-        set_wave_priority(s.hit ? (fminf(s.X, lat.tmax) - fmaxf(s.E, lat.tmin)) *
+        set_wave_priority(s.hit ? (fminf(s.m.X, lat.tmax) - fmaxf(s.m.E, lat.tmin)) *
                                       (fabsf(d[0]) * g.geom[6] + fabsf(d[1]) * g.geom[7] + fabsf(d[2]) * g.geom[8])
                                 : 0.0f,
                           g.R);
         if (i >= 0) {
             const CountCtx ctx{lat, pool};
             CountVis vis = make_count_vis(i, pool);
-            if (s.hit) march_segment<kGrid, kSkip>(g, tree, 0, s.ray, s.E, s.X, lat, vis, ctx);
+            if (s.hit) march_segment<kGrid, kSkip>(g, tree, 0, s.ray, s.m, s.m.E, s.m.X, lat, vis, ctx);
             vis.finish(ctx);
             n = vis.n;
             counts[i] = n;

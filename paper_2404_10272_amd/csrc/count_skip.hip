@@ -1,7 +1,7 @@
 // The counting pass's Alg. 2 (skip) walks over a VDB tree: hierarchical,
 // voxel and sub-leaf steps, single- and multi-level, tree in LDS or not.
-// They live in a source of their own so the build can compile them at -O2
-// while the rest of the sampler is built at -O1; sample.hip launches them.
+// In a source of their own only to compile beside the rest; sample.hip
+// launches them.
 #pragma clang fp contract(off)
 
 #include "count.hpp"

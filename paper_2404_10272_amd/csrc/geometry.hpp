@@ -51,13 +51,9 @@ struct Axis {
         float uf = pos ? vf : (float)(R - 1) - vf;
         uf = fminf(fmaxf(uf, -1.0f), (float)R);   // NaN -> -1
         int u = (int)uf;
-        if (inclusive) {
-            while (u >= 0 && !(Tk(u) <= t)) --u;
-            while (u < R && Tk(u + 1) <= t) ++u;
-        } else {
-            while (u >= 0 && !(Tk(u) < t)) --u;
-            while (u < R && Tk(u + 1) < t) ++u;
-        }
+        const auto before = [&](float T) { return T < t || (inclusive && T == t); };
+        while (u >= 0 && !before(Tk(u))) --u;
+        while (u < R && before(Tk(u + 1))) ++u;
         return u;
     }
 
@@ -70,21 +66,6 @@ struct Axis {
         while (v >= 0 && plane(v) > o) --v;
         while (v < R && plane(v + 1) <= o) ++v;
         return v;
-    }
-
-    // Advance ray-order voxel u (known to satisfy Tk(u) <= t) to the
-    // voxel owning the parameters just after t, without passing u_hi: the
-    // largest e in [u, u_hi] with Tk(e) <= t, by binary search on the exact
-    // crossings (they never decrease along the ray).  Needs no position
-    // estimate, so a walk keeps no estimate inputs live for it.
-    __device__ __forceinline__ int advance_to(int u, float t, int u_hi) const {
-        int lo = u, hi = u_hi;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (Tk(mid) <= t) lo = mid;
-            else hi = mid - 1;
-        }
-        return lo;
     }
 };
 
@@ -104,27 +85,6 @@ __device__ __forceinline__ Axis load_axis(const float *geom, int lev, int a, int
     x.pos = d > 0.0f;
     x.zero = (d == 0.0f) || __builtin_isinf(r);
     return x;
-}
-
-// Entry/exit parameters (E, X] of the level box: max over moving axes of the
-// first plane crossing, min of the last; zero axes must hold o inside.
-// Returns false when the level is missed (or the interval is empty).
-__device__ __forceinline__ bool level_span(const Axis &ax, const Axis &ay, const Axis &az, float &E, float &X) {
-    E = -__builtin_huge_valf();
-    X = __builtin_huge_valf();
-    const Axis *axes[3] = {&ax, &ay, &az};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const Axis &A = *axes[a];
-        if (A.zero) {
-            int v = A.zero_voxel();
-            if (v < 0 || v >= A.R) return false;
-        } else {
-            E = fmaxf(E, A.Tk(0));
-            X = fminf(X, A.Tk(A.R));
-        }
-    }
-    return E < X;
 }
 
 // ---------------------------------------------------------------- lattice

@@ -27,42 +27,154 @@ constexpr int kBlock = 256;
 
 // ------------------------------------------------------------------ cursors
 
-// Dense bitfield: every cell is a voxel; one bit lookup per voxel.
-struct DenseCursor {
-    const uint32_t *bits;
-    uint64_t level_base;  // bit index of the level's voxel (0,0,0)
-    int R;
-    Axis A0, A1, A2;
-    int u0, u1, u2;       // ray-order voxel per moving axis
-    int v0, v1, v2;       // voxel index per axis
-    float tn0, tn1, tn2;  // next plane crossing per axis (+inf for zero axes)
+// One moving axis as a cursor steps along it, in "walk order": the voxel
+// coordinate w rises by one per voxel crossed -- w = v for d > 0, w = ~v for
+// d < 0, so blocks of 2^k voxels stay aligned in w -- and the plane a step out
+// of w crosses is p = w + 1, crossed at
+//   T(p) = fl(fl(fl(B + fl(p * hs)) - o) * r),   hs = h or -h,
+// which is the plane crossing of the definition bit for bit (a sign moved
+// through a product changes no rounding).  T never decreases along the ray.
+// An axis that does not move has hs = 0, o = -inf, r = 1: every T is +inf,
+// with no test on any step.
+struct WalkAxis {
+    float B, hs, o, r;
+    float per;      // approximate voxels per unit of parameter, for relocation
+    int32_t flip;   // v = w ^ flip
 
-    __device__ __forceinline__ bool occupied() const {
-        uint64_t idx = level_base + ((uint64_t)((uint32_t)v0 * (uint32_t)R + (uint32_t)v1) * (uint32_t)R + (uint32_t)v2);
-        return (bits[idx >> 5] >> (idx & 31)) & 1u;
+    __device__ __forceinline__ float T(float p) const {
+        return __fmul_rn(__fsub_rn(__fadd_rn(B, __fmul_rn(p, hs)), o), r);
     }
-    __device__ __forceinline__ float exit(int &axis) const {
-        float hi = tn0;
-        axis = 0;
-        if (tn1 < hi) { hi = tn1; axis = 1; }
-        if (tn2 < hi) { hi = tn2; axis = 2; }
-        return hi;
+    __device__ __forceinline__ float T(int p) const { return T((float)p); }
+};
+
+// Axis a of level `lev` for a ray: plane geometry from the level's table
+// (B, h = fl((A-B)/R)), origin and direction component and its correctly
+// rounded reciprocal.  d == 0 and an infinite 1/d do not move.
+__device__ __forceinline__ bool axis_moves(float d, float r) { return d != 0.0f && !__builtin_isinf(r); }
+
+__device__ __forceinline__ WalkAxis walk_axis(const float *geom, int lev, int a, float o, float d, float r) {
+    const float B = geom[12 * lev + a], h = geom[12 * lev + 3 + a];
+    const bool moves = axis_moves(d, r);
+    WalkAxis x;
+    x.B = B;
+    x.hs = moves ? (d > 0.0f ? h : -h) : 0.0f;
+    x.o = moves ? o : -__builtin_huge_valf();
+    x.r = moves ? r : 1.0f;
+    x.per = __builtin_amdgcn_rcpf(x.hs * x.r);
+    x.flip = moves && d < 0.0f ? -1 : 0;
+    return x;
+}
+
+// Relocation after a step out of a cell larger than a voxel: the walk-order
+// voxel of each axis that holds the parameters just after t, the largest e in
+// [w, p-1] with T(e) <= t (w itself when w >= p), for a ray known to be in
+// voxels w .. p-1 then (T(w) <= t <= T(p) = Tp).
+//
+// With real arithmetic that is p - ceil(q), q = (Tp - t) / (h |r|) voxels
+// back from p.  Rounding moves a crossing by less than
+// |r| 2^-24 (6.1 M + 3.1 |o|), M the largest plane coordinate, so two of them
+// move q by less than 2^-20 (M + |o|) / h; computing q adds a relative 2^-21
+// of at most 2^8 voxels.  Where q is further than `slack` (twice both bounds)
+// from an integer, the estimate is the answer; elsewhere, one time in about
+// a thousand, exact comparisons settle it, as they do for a NaN or infinite
+// q.  Ten instructions an axis, where a binary search over eight voxels takes
+// about thirty.
+__device__ __forceinline__ float relocate_slack(const float *geom, int lev, int R, const float o[3]) {
+    float s = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float B = geom[12 * lev + a], h = geom[12 * lev + 3 + a];
+        s = fmaxf(s, (fmaxf(fabsf(B), fabsf(B + (float)R * h)) + fabsf(o[a])) * geom[12 * lev + 6 + a]);
     }
-    __device__ __forceinline__ bool step(int axis, float) {
-        if (axis == 0) {
-            if (++u0 >= R) return false;
-            v0 = A0.voxel(u0);
-            tn0 = A0.Tk(u0 + 1);
-        } else if (axis == 1) {
-            if (++u1 >= R) return false;
-            v1 = A1.voxel(u1);
-            tn1 = A1.Tk(u1 + 1);
-        } else {
-            if (++u2 >= R) return false;
-            v2 = A2.voxel(u2);
-            tn2 = A2.Tk(u2 + 1);
-        }
-        return true;
+    return s * 0x1p-19f + 0x1p-12f;
+}
+
+struct Relocation {
+    int e;
+    bool sure;
+};
+__device__ __forceinline__ Relocation relocate_estimate(const WalkAxis &A, int w, int p, float Tp, float t,
+                                                        float slack) {
+    const float q = (Tp - t) * A.per;
+    // an axis that stepped is at w = p: there is nothing to settle
+    return {(int)fmaxf((float)p - ceilf(q), (float)w), fabsf(q - rintf(q)) > slack || w >= p};
+}
+__device__ __forceinline__ int relocate_exact(const WalkAxis &A, int e, int w, int p, float t) {
+    e = max(min(e, p - 1), w);
+    while (e > w && A.T(e) > t) --e;
+    while (e + 1 < p && A.T(e + 1) <= t) ++e;
+    return e;
+}
+__device__ __forceinline__ void relocate(const WalkAxis &A0, const WalkAxis &A1, const WalkAxis &A2, int &w0, int &w1,
+                                         int &w2, int p0, int p1, int p2, float t0, float t1, float t2, float t,
+                                         float slack) {
+    const Relocation a0 = relocate_estimate(A0, w0, p0, t0, t, slack);
+    const Relocation a1 = relocate_estimate(A1, w1, p1, t1, t, slack);
+    const Relocation a2 = relocate_estimate(A2, w2, p2, t2, t, slack);
+    int e0 = a0.e, e1 = a1.e, e2 = a2.e;
+    if (!(a0.sure & a1.sure & a2.sure)) {
+        e0 = relocate_exact(A0, e0, w0, p0, t);
+        e1 = relocate_exact(A1, e1, w1, p1, t);
+        e2 = relocate_exact(A2, e2, w2, p2, t);
+    }
+    w0 = e0;
+    w1 = e1;
+    w2 = e2;
+}
+
+// The cursors share one step: exit() gives the parameter hi at which the ray
+// leaves the current cell -- the smallest of the three axes' crossings, all
+// computed on every step -- and advance(hi) moves every axis whose crossing
+// is hi across its plane.  Computing all three and selecting costs fewer
+// issue slots than one branch per axis, of which a wave runs each in turn
+// because its lanes step along different axes.  Axes that tie step together:
+// the cell between them would hold (hi, hi], no parameter at all.  A walk
+// needs no test for leaving the grid: it ends when hi reaches the segment's
+// end b, which is at most the first crossing of a last plane, and crossings
+// never decrease, so a plane crossed at hi < b is not a last one.
+
+// Dense bitfield: every cell is a voxel; one bit lookup per voxel.  The bit
+// read for the new voxel is tested in the next step, after that step's
+// crossings, so its latency overlaps them.
+struct DenseCursor {
+    const uint32_t *bits;   // word holding the level's first bits
+    WalkAxis A0, A1, A2;
+    float p0, p1, p2;       // next plane per axis, as a float (exact: at most 2^10)
+    float t0, t1, t2;       // its crossing
+    int32_t s0, s1, s2;     // bit-index change of a step along each axis
+    uint32_t idx;           // bit index of the current voxel
+    uint32_t word;          // its word
+
+    // by a 32-bit byte offset from a uniform base (a level has at most 2^30 bits)
+    __device__ __forceinline__ void fetch() {
+        word = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(bits) + ((idx >> 5) << 2));
+    }
+    __device__ __forceinline__ void start(const uint32_t *all, uint64_t level_base, int R, int w0, int w1, int w2) {
+        bits = all + (level_base >> 5);
+        const int v0 = w0 ^ A0.flip, v1 = w1 ^ A1.flip, v2 = w2 ^ A2.flip;
+        idx = (uint32_t)(level_base & 31) + ((uint32_t)v0 * (uint32_t)R + (uint32_t)v1) * (uint32_t)R + (uint32_t)v2;
+        s0 = ((R * R) ^ A0.flip) - A0.flip;
+        s1 = (R ^ A1.flip) - A1.flip;
+        s2 = 1 | A2.flip;
+        p0 = (float)(w0 + 1);
+        p1 = (float)(w1 + 1);
+        p2 = (float)(w2 + 1);
+        fetch();
+    }
+    __device__ __forceinline__ uint32_t occupied() const { return (word >> (idx & 31)) & 1u; }
+    __device__ __forceinline__ float exit() {
+        t0 = A0.T(p0);
+        t1 = A1.T(p1);
+        t2 = A2.T(p2);
+        return fminf(fminf(t0, t1), t2);
+    }
+    __device__ __forceinline__ void advance(float hi) {
+        const bool c0 = t0 <= hi, c1 = t1 <= hi, c2 = t2 <= hi;
+        p0 += c0 ? 1.0f : 0.0f;
+        p1 += c1 ? 1.0f : 0.0f;
+        p2 += c2 ? 1.0f : 0.0f;
+        idx += (uint32_t)(c0 ? s0 : 0) + (uint32_t)(c1 ? s1 : 0) + (uint32_t)(c2 ? s2 : 0);
+        fetch();
     }
 };
 
@@ -153,202 +265,173 @@ __device__ __forceinline__ Tree load_tree(const GridView &g, uint32_t *smem) {
 // 4^3 sub-block (D = 4: all its 64 voxels empty, or all occupied), so that
 // the cells nest as aligned cubes of 8S, 8, 4 and 1 voxels a side and a step
 // passes empty space by powers of two down to single voxels (Fig. 1).
-// The cell's exit is the first crossing of its far planes (for D = 1 the
-// ordinary voxel step).
 //
-// The walk is incremental, as in a plain DDA: a step moves the stepping axis
-// into the next cell and looks that cell up; when it has the same size as the
-// cell left, only the stepping axis's exit plane moves (D planes further).
-// The other axes stay inside their D-aligned blocks while tiles are crossed,
-// so their voxels are only re-located (exactly, at the exit parameter) when
-// the walk descends into a finer cell; a change of size recomputes all three
-// exits.  Cell sequence and exit parameters equal those of a walk that
-// re-locates every axis at every exit.
+// Cells are aligned in walk order too, so the exit plane of an axis is
+// (w | (D-1)) + 1 whatever its direction.  While cells of one size or larger
+// are crossed, the axes that do not step keep a voxel that may lie behind the
+// ray but is in the same cell; only on the way into a finer cell are they
+// relocated, exactly, at the exit parameter.  The 8^3 block entered is known
+// before that (axes inside an 8^3 tile stay in its block), so the relocation
+// follows the slot lookup and nothing is looked up twice.
+//
+// The slot table is read only when the block changes; the leaf's word is read
+// for every leaf voxel and tested in the next step, after that step's
+// crossings, so the walk waits for LDS but not for memory.
 //
 // kTiles = false walks the same tree one voxel per step (the paper's
 // "VDB + DDA" rows, Tab. 1-2): a voxel inside a tile takes the tile's value
 // and the walk moves on to the next voxel, so the tree only changes how
 // occupancy is looked up, not which cells are visited.
-//
-// kSub trades steps for dearer ones: it takes a fifth to a quarter fewer steps, but
-// the cell size changes more often inside leaves, and each change recomputes
-// all exits (and, going down, re-locates the other axes and looks the cell up
-// again), in some lane of most steps of a wave.  Only 4^3 sub-blocks are
-// cells: adding the 2^3 ones (D = 2) saves a few more steps but changes the
-// size about twice as often again, which costs more than it saves (object
-// walk 0.230 against 0.209 ms, four cascades the same).
 template <bool kTiles, bool kSub = false>
 struct VdbWalk {
     Tree t;
-    int lev, R, sh;
-    Axis A0, A1, A2;
-    int u0, u1, u2;        // ray-order voxel per moving axis (inside the current cell's block)
-    int v0, v1, v2;        // voxel index per axis
-    int k0, k1, k2;        // ray-order exit plane of the current cell per moving axis
-    float e0, e1, e2;      // their crossing parameters (+inf for zero axes)
-    int kx;                // exit plane of the axis exit() chose
-    int D;                 // current cell size in voxels
-    bool occ;              // current cell occupied
-    int lblk;              // cached leaf block (packed block coordinates), -1 if none
-    int lbase;             // its first word in the leaf array
-    uint32_t lu4;          // its uniform 4^3 sub-blocks (its Tree::sub entry)
+    int lev;
+    int node;              // first slot of the current root cell's node, or the cell's tile value
+    WalkAxis A0, A1, A2;
+    int w0, w1, w2;        // voxel in walk order (inside the current cell)
+    int p0, p1, p2;        // exit plane of the current cell
+    float t0, t1, t2;      // its crossing
+    float slack;           // relocate_slack
+    int Dm1;               // current cell size in voxels, less one
+    int lblk;              // 8^3 block last looked up (packed block coordinates), -1 if none
+    int code;              // its table entry: leaf index, or a tile's value (kEmptyTile ...)
+    uint32_t word, bit;    // current cell occupied: bit `bit` of `word`
+    uint32_t lu4;          // kSub: uniform 4^3 sub-blocks of the leaf
 
-    // Size of the largest uniform cell holding voxel (v0, v1, v2) and its
-    // occupancy.  A voxel in the cached leaf block (most voxel steps) needs
-    // only its word and bit; otherwise the root and slot tables are read and
-    // a leaf found there becomes the cached one.  The word is read on every
-    // leaf voxel: keeping the last one costs a divergent branch per step,
-    // which is dearer than the (cached) load.
-    __device__ __forceinline__ int classify(bool &o) {
-        const int blk = ((v0 >> 3) << 20) | ((v1 >> 3) << 10) | (v2 >> 3);
-        int D = 1;
+    // table entries of tiles; even entries are occupied
+    static constexpr int kEmptySlot = -1, kFullSlot = -2, kEmptyRoot = -3, kFullRoot = -4;
+
+    __device__ __forceinline__ void set_node(int r) { node = r < 0 ? r - 2 : r << (3 * t.ilog2); }
+    __device__ __forceinline__ void relocate_at(float hi) {
+        relocate(A0, A1, A2, w0, w1, w2, p0, p1, p2, t0, t1, t2, hi, slack);
+    }
+
+    // The cell holding the current voxels, entered at hi from a cell of size
+    // Dm1 + 1 (0: the voxels are exact), becomes current.
+    __device__ __forceinline__ void lookup(float hi) {
+        int v0 = w0 ^ A0.flip, v1 = w1 ^ A1.flip, v2 = w2 ^ A2.flip;
+        const int blk = ((v0 >> 3) << 14) | ((v1 >> 3) << 7) | (v2 >> 3);
         if (blk != lblk) {
-            const int NR = t.NR;
-            const int ri = NR == 1 ? lev : ((lev * NR + (v0 >> sh)) * NR + (v1 >> sh)) * NR + (v2 >> sh);
-            const int node = t.root[ri];
-            const int lg = t.ilog2, m = t.S - 1;
-            const int s = (((v0 >> 3) & m) << (2 * lg)) | (((v1 >> 3) & m) << lg) | ((v2 >> 3) & m);
-            const int c = t.slot[(max(node, 0) << (3 * lg)) | s];
-            const bool root_tile = node < 0;
-            const bool slot_tile = !root_tile && c < 0;
-            if (!root_tile && !slot_tile) {
-                lblk = blk;
-                lbase = c * 8;
-                if (kSub) lu4 = (uint32_t)t.sub[c];
-            } else {
-                o = root_tile ? node == -2 : c == -2;
-                return kTiles ? (root_tile ? (8 << t.ilog2) : 8) : 1;
+            lblk = blk;
+            const int NR = t.NR, lg = t.ilog2;
+            if (NR > 1) {
+                const int sh = 3 + lg;
+                set_node(t.root[((lev * NR + (v0 >> sh)) * NR + (v1 >> sh)) * NR + (v2 >> sh)]);
             }
+            const int m = t.S - 1;
+            const int s = (((((v0 >> 3) & m) << lg) | ((v1 >> 3) & m)) << lg) | ((v2 >> 3) & m);
+            const int c = t.slot[max(node, 0) + s];
+            code = node < 0 ? node : c;
+            if (kSub && code >= 0) lu4 = (uint32_t)t.sub[code];
         }
-        const uint64_t word = t.leaves[lbase + (v0 & 7)];
-        const int bit = ((v1 & 7) << 3) | (v2 & 7);
-        const uint32_t half = bit < 32 ? (uint32_t)word : (uint32_t)(word >> 32);
-        o = ((half >> (bit & 31)) & 1u) != 0;
-        if (kSub) {
-            // a uniform 4^3 sub-block takes the voxel's value and is the cell
-            const int s4 = (((v0 >> 2) & 1) << 2) | (((v1 >> 2) & 1) << 1) | ((v2 >> 2) & 1);
-            D = ((lu4 >> s4) & 1u) != 0 ? 4 : 1;
-        }
-        return D;
-    }
-
-    // exit planes and parameters of every moving axis for cells of size D.
-    // Every axis is computed and a zero axis's parameter replaced by +inf
-    // afterwards: a per-axis branch here costs more than the arithmetic.
-    __device__ __forceinline__ void exits_all() {
-        const float inf = __builtin_huge_valf();
-        const int msk = ~(D - 1);
-        const int b0 = v0 & msk, b1 = v1 & msk, b2 = v2 & msk;
-        k0 = A0.pos ? b0 + D : R - b0;
-        k1 = A1.pos ? b1 + D : R - b1;
-        k2 = A2.pos ? b2 + D : R - b2;
-        e0 = A0.zero ? inf : A0.Tk(k0);
-        e1 = A1.zero ? inf : A1.Tk(k1);
-        e2 = A2.zero ? inf : A2.Tk(k2);
-    }
-
-    // the cell holding the current voxels becomes current
-    __device__ __forceinline__ void enter() {
-        bool o;
-        D = classify(o);
-        occ = o;
-        exits_all();
-    }
-
-    __device__ __forceinline__ bool occupied() const { return occ; }
-
-    // first exit crossing; also keeps that axis's exit plane for step()
-    __device__ __forceinline__ float exit(int &axis) {
-        float hi = e0;
-        int k = k0;
-        axis = 0;
-        if (e1 < hi) { hi = e1; k = k1; axis = 1; }
-        if (e2 < hi) { hi = e2; k = k2; axis = 2; }
-        kx = k;
-        return hi;
-    }
-
-    // moves into the next cell across the exit found by exit(); false when
-    // that leaves the grid
-    __device__ __forceinline__ bool step(int axis, float t) {
-        const int ka = kx;
-        if (ka >= R) return false;
-        if (axis == 0) { u0 = ka; v0 = A0.voxel(ka); }
-        if (axis == 1) { u1 = ka; v1 = A1.voxel(ka); }
-        if (axis == 2) { u2 = ka; v2 = A2.voxel(ka); }
-        bool o;
-        int Dn = classify(o);
-        if (Dn == D) {
-            // same cell size: the next exit along the stepping axis is D planes on
-            if (axis == 0) { k0 += D; e0 = A0.Tk(k0); }
-            if (axis == 1) { k1 += D; e1 = A1.Tk(k1); }
-            if (axis == 2) { k2 += D; e2 = A2.Tk(k2); }
+        if (code >= 0) {
+            if (kTiles && Dm1 != 0) {
+                relocate_at(hi);
+                v0 = w0 ^ A0.flip;
+                v1 = w1 ^ A1.flip;
+                v2 = w2 ^ A2.flip;
+            }
+            const uint32_t at = ((((uint32_t)v0 & 7) << 3 | ((uint32_t)v1 & 7)) << 3) | ((uint32_t)v2 & 7);
+            // a 32-bit byte offset from a uniform base (at most 2^24 leaves of 64 bytes)
+            word = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(t.leaves) +
+                                                       (((uint32_t)code << 6) | ((at >> 5) << 2)));
+            bit = at & 31;
+            Dm1 = 0;
+            if (kSub) {
+                // a uniform 4^3 sub-block takes the voxel's value and is the cell
+                const int s4 = ((v0 & 4) | ((v1 & 4) >> 1) | ((v2 & 4) >> 2));
+                Dm1 = ((lu4 >> s4) & 1u) != 0 ? 3 : 0;
+            }
         } else {
-            if (Dn < D) {
-                // descending out of a tile: voxels of the other axes at t, inside their blocks
-                if (axis != 0 && !A0.zero) { u0 = A0.advance_to(u0, t, min(k0, R) - 1); v0 = A0.voxel(u0); }
-                if (axis != 1 && !A1.zero) { u1 = A1.advance_to(u1, t, min(k1, R) - 1); v1 = A1.voxel(u1); }
-                if (axis != 2 && !A2.zero) { u2 = A2.advance_to(u2, t, min(k2, R) - 1); v2 = A2.voxel(u2); }
-                Dn = classify(o);
-            }
-            D = Dn;
-            exits_all();
+            word = ~(uint32_t)code;   // bit 0: an even entry is occupied
+            bit = 0;
+            if (kTiles) Dm1 = code <= kEmptyRoot ? (8 << t.ilog2) - 1 : 7;
         }
-        occ = o;
-        return true;
+    }
+
+    __device__ __forceinline__ uint32_t occupied() const { return (word >> bit) & 1u; }
+
+    __device__ __forceinline__ float exit() {
+        p0 = (w0 | Dm1) + 1;
+        p1 = (w1 | Dm1) + 1;
+        p2 = (w2 | Dm1) + 1;
+        t0 = A0.T(p0);
+        t1 = A1.T(p1);
+        t2 = A2.T(p2);
+        return fminf(fminf(t0, t1), t2);
+    }
+
+    __device__ __forceinline__ void advance(float hi) {
+        w0 = t0 <= hi ? p0 : w0;
+        w1 = t1 <= hi ? p1 : w1;
+        w2 = t2 <= hi ? p2 : w2;
+        // out of a root tile the other axes may be in another block
+        if (kTiles && Dm1 > 7) {
+            relocate_at(hi);
+            Dm1 = 0;
+        }
+        lookup(hi);
     }
 };
 
 // ------------------------------------------------------------------ driver
 
 // Walks cells from the segment start a to its end b (or t_max) and reports
-// maximal occupied runs (lo, hi] to the visitor, from a single call site.
+// maximal occupied runs (lo, hi] to the visitor.
 // kSkip = false is Alg. 1 (every cell visited, branch on occupancy);
 // kSkip = true is Alg. 2 (an inner loop passes all leading empty cells, then
 // the occupied run is marched).
+//
+// A visitor that has no room for another run (vis.room) makes the loop of
+// Alg. 1 stop on the cell that would close it; vis.make_room, outside the
+// loop, empties its store, and the walk goes on from the same cell.
 template <bool kSkip, class Cursor, class Vis, class Ctx>
 __device__ __forceinline__ void drive(Cursor &c, float a, float b, float tmax, Vis &vis, const Ctx &ctx) {
     float lo = a;
+    const float last = fminf(b, tmax);
     if (!kSkip) {
-        bool in_run = false;
+        uint32_t in_run = 0;
         float run_lo = a;
         while (true) {
-            bool occ = c.occupied();
-            int axis;
-            float hi = c.exit(axis);
-            if (occ && !in_run) {
-                in_run = true;
-                run_lo = lo;
+            bool full = false;
+            while (true) {
+                const float hi = c.exit();
+                const bool end = hi >= last;
+                const uint32_t occ = c.occupied();
+                if (occ > in_run) run_lo = lo;
+                // a run closes at lo on an empty cell, or at this cell's end when the ray ends
+                if ((in_run > occ) | (end & (occ != 0))) {
+                    full = !vis.room(ctx);
+                    if (full) break;
+                    vis.run(ctx, run_lo, occ != 0 ? fminf(hi, b) : lo);
+                }
+                if (end) break;
+                in_run = occ;
+                c.advance(hi);
+                lo = hi;
             }
-            bool end = hi >= b || hi >= tmax;
-            if (!end) end = !c.step(axis, hi);
-            // a run closes at lo on an empty cell, or at this cell's end when the ray ends
-            if (in_run && (!occ || end)) {
-                vis.run(ctx, run_lo, occ ? fminf(hi, b) : lo);
-                in_run = false;
-            }
-            if (end) return;
-            lo = hi;
+            if (!full) return;
+            vis.make_room(ctx);
         }
     } else {
         while (true) {
             bool end = false;
             while (!c.occupied()) {
-                int axis;
-                float hi = c.exit(axis);
-                if (hi >= b || hi >= tmax || !c.step(axis, hi)) return;
+                const float hi = c.exit();
+                if (hi >= last) return;
+                c.advance(hi);
                 lo = hi;
             }
             float run_lo = lo, run_hi;
             while (true) {
-                int axis;
-                float hi = c.exit(axis);
-                end = hi >= b || hi >= tmax;
-                if (!end) end = !c.step(axis, hi);
+                const float hi = c.exit();
+                end = hi >= last;
+                if (!end) c.advance(hi);
                 run_hi = fminf(hi, b);
                 lo = hi;
                 if (end || !c.occupied()) break;
             }
+            if (!vis.room(ctx)) vis.make_room(ctx);
             vis.run(ctx, run_lo, run_hi);
             if (end) return;
         }
@@ -369,7 +452,9 @@ __device__ __forceinline__ void drive(Cursor &c, float a, float b, float tmax, V
 // a loop over the ray's recorded runs that also merges adjacent ranges and
 // rewrites them in place.  Lanes close runs at different steps, so doing the
 // lattice arithmetic at the close would run it, masked, in most steps of a
-// wave; after the walk the lanes of a wave do it together.
+// wave; after the walk the lanes of a wave do it together.  A ray whose runs
+// are lost records into its fixed slots again and again; each time they are
+// full the walk stops and they are counted and dropped (make_room).
 constexpr int kMaxRuns = 16;
 constexpr int32_t kRunsLost = 0x7fffffff;
 
@@ -393,95 +478,109 @@ struct CountCtx {
 
 // Per-lane state of the count pass.
 struct CountVis {
-    int32_t n;            // samples
-    int32_t nr;           // runs recorded (kRunsLost: pool exhausted); after finish(), runs kept
-    int32_t kept;         // runs recorded before the pool ran dry
+    int2 *at;             // where the next run is recorded
     int64_t ray;
-    int32_t first;        // first pool chunk of the ray, -1 if none
-    int32_t chunk;        // last pool chunk taken
+    int32_t n;            // samples counted so far (of a lost ray before finish(), else 0)
+    int32_t nr;           // runs recorded and not yet counted; after finish(), runs kept or kRunsLost
+    int32_t chunk;        // last pool chunk taken, -1 if none, kDry once the pool has run dry
+    static constexpr int32_t kDry = -2;
 
-    __device__ __forceinline__ void begin_level(int, const Axis &, const Axis &, const Axis &) {}
+    __device__ __forceinline__ void begin_level(const GridView &, int, const float *, const float *) {}
 
-    // slot k of the ray (k >= kMaxRuns: slot k % kMaxRuns of pool chunk c)
-    __device__ __forceinline__ int2 *slot(const RunPool &pool, int k, int32_t c) const {
-        return k < kMaxRuns ? pool.slots + (int64_t)k * pool.stride + ray : pool.chunks + (int64_t)c * kMaxRuns + k % kMaxRuns;
-    }
-    // records run nr; false (and the ray marked lost) if the pool is dry
-    __device__ __forceinline__ bool record(const RunPool &pool, int2 v) {
-        if (nr >= kMaxRuns && nr % kMaxRuns == 0) {
-            const int32_t c = atomicAdd(pool.head, 1);
-            if (c >= pool.cap) {
-                kept = nr;
-                nr = kRunsLost;
-                return false;
-            }
-            pool.chunk_next[c] = -1;
-            if (nr == kMaxRuns) {
-                pool.ray_next[ray] = c;
-                first = c;
-            } else {
-                pool.chunk_next[chunk] = c;
-            }
-            chunk = c;
-        }
-        *slot(pool, nr, chunk) = v;
-        ++nr;
+    // room for one more run; takes the next pool chunk when the slots so far are used
+    __device__ __forceinline__ bool room(const CountCtx &x) {
+        const RunPool &pool = x.pool;
+        if (nr == 0 || nr % kMaxRuns != 0) return true;
+        if (chunk == kDry) return false;
+        const int32_t c = atomicAdd(pool.head, 1);
+        if (c >= pool.cap) return false;
+        pool.chunk_next[c] = -1;
+        if (nr == kMaxRuns) pool.ray_next[ray] = c;
+        else pool.chunk_next[chunk] = c;
+        chunk = c;
+        at = pool.chunks + (int64_t)c * kMaxRuns;
         return true;
+    }
+    __device__ __forceinline__ void run(const CountCtx &x, float lo, float hi) {
+        *at = make_int2(__float_as_int(lo), __float_as_int(hi));
+        at += nr < kMaxRuns ? x.pool.stride : 1;
+        ++nr;
+    }
+    // The pool is dry: the runs recorded so far are counted and dropped (the
+    // fill re-walks this ray, so only its count is needed).
+    __device__ __forceinline__ void make_room(const CountCtx &x) {
+        walk_runs<false>(x);
+        chunk = kDry;
+        nr = 0;
+        at = x.pool.slots + ray;
     }
     // lattice points of (lo, hi] up to t_max: [n0, n1), empty when n1 <= n0
     __device__ __forceinline__ static int2 lattice_range(const Lattice &lat, float lo, float hi) {
         return make_int2(lat.first_above(lo), lat.first_above(fminf(hi, lat.tmax)));
     }
-    __device__ __forceinline__ void run(const CountCtx &x, float lo, float hi) {
-        if (nr != kRunsLost && record(x.pool, make_int2(__float_as_int(lo), __float_as_int(hi)))) return;
-        // the pool is dry: this ray is re-walked by the fill, only its count is needed
-        const int2 q = lattice_range(x.lat, lo, hi);
-        n += max(q.y - q.x, 0);
-    }
-    // Lattice ranges of the recorded runs, merged where one ends at the next's
-    // start and written back over the recorded runs (the write index never
-    // passes the read index).
-    __device__ __forceinline__ void finish(const CountCtx &x) {
-        const bool lost = nr == kRunsLost;
-        const int m = lost ? kept : nr;
-        int w = 0;
+    // Adds the lattice points of the nr recorded runs to n.  kKeep: the
+    // ranges, merged where one ends at the next's start, are written back
+    // over the recorded runs (the write index never passes the read index),
+    // and nr becomes their number.
+    template <bool kKeep>
+    __device__ __forceinline__ void walk_runs(const CountCtx &x) {
+        const RunPool &pool = x.pool;
+        const int64_t stride = pool.stride;
+        int2 *rp = pool.slots + ray, *wp = rp;
+        int32_t rc = -1, wc = -1;        // pool chunks of the read and write positions
         int32_t c0 = 0, c1 = 0;          // merged range held back (c1 > c0 when held)
-        int32_t rc = first, wc = first;  // pool chunks of the read and write positions
-        for (int k = 0; k < m; ++k) {
-            if (k > kMaxRuns && k % kMaxRuns == 0) rc = x.pool.chunk_next[rc];
-            const int2 raw = *slot(x.pool, k, rc);
+        int w = 0;
+        const auto next = [&](int2 *&q, int32_t &c, int k) {   // q moves on to position k
+            if (k < kMaxRuns) q += stride;
+            else if (k % kMaxRuns != 0) q += 1;
+            else {
+                c = k == kMaxRuns ? pool.ray_next[ray] : pool.chunk_next[c];
+                q = pool.chunks + (int64_t)c * kMaxRuns;
+            }
+        };
+        const auto emit = [&]() {
+            if (w > 0) next(wp, wc, w);
+            *wp = make_int2(c0, c1);
+            ++w;
+        };
+        for (int k = 0; k < nr; ++k) {
+            if (k > 0) next(rp, rc, k);
+            const int2 raw = *rp;
             const int2 q = lattice_range(x.lat, __int_as_float(raw.x), __int_as_float(raw.y));
             if (q.y <= q.x) continue;
             n += q.y - q.x;
-            if (c1 > c0 && c1 == q.x) {
+            if (kKeep) {
+                if (c1 > c0 && c1 == q.x) {
+                    c1 = q.y;
+                    continue;
+                }
+                if (c1 > c0) emit();
+                c0 = q.x;
                 c1 = q.y;
-                continue;
             }
-            if (c1 > c0 && !lost) {
-                if (w > kMaxRuns && w % kMaxRuns == 0) wc = x.pool.chunk_next[wc];
-                *slot(x.pool, w, wc) = make_int2(c0, c1);
-                ++w;
-            }
-            c0 = q.x;
-            c1 = q.y;
         }
-        if (c1 > c0 && !lost) {
-            if (w > kMaxRuns && w % kMaxRuns == 0) wc = x.pool.chunk_next[wc];
-            *slot(x.pool, w, wc) = make_int2(c0, c1);
-            ++w;
+        if (kKeep) {
+            if (c1 > c0) emit();
+            nr = w;
         }
-        if (lost) x.pool.lost[atomicAdd(x.pool.n_lost, 1)] = (int32_t)ray;
-        else nr = w;
+    }
+    __device__ __forceinline__ void finish(const CountCtx &x) {
+        if (chunk != kDry) {
+            walk_runs<true>(x);
+            return;
+        }
+        walk_runs<false>(x);
+        nr = kRunsLost;
+        x.pool.lost[atomicAdd(x.pool.n_lost, 1)] = (int32_t)ray;
     }
 };
 
 __device__ __forceinline__ CountVis make_count_vis(int64_t ray, const RunPool &pool) {
     CountVis v;
+    v.at = pool.slots + ray;
+    v.ray = ray;
     v.n = 0;
     v.nr = 0;
-    v.kept = 0;
-    v.ray = ray;
-    v.first = -1;
     v.chunk = -1;
     pool.ray_next[ray] = -1;
     return v;
@@ -505,14 +604,16 @@ struct FillVis {
     int lev;
     Axis A0, A1, A2;      // level geometry, for voxel ids only
 
-    __device__ __forceinline__ void begin_level(int l, const Axis &a0, const Axis &a1, const Axis &a2) {
+    __device__ __forceinline__ void begin_level(const GridView &g, int l, const float *o, const float *d) {
         lev = l;
         if (kVox) {
-            A0 = a0;
-            A1 = a1;
-            A2 = a2;
+            A0 = load_axis(g.geom, l, 0, g.R, o[0], d[0], __fdiv_rn(1.0f, d[0]));
+            A1 = load_axis(g.geom, l, 1, g.R, o[1], d[1], __fdiv_rn(1.0f, d[1]));
+            A2 = load_axis(g.geom, l, 2, g.R, o[2], d[2], __fdiv_rn(1.0f, d[2]));
         }
     }
+    __device__ __forceinline__ bool room(const FillCtx &) { return true; }
+    __device__ __forceinline__ void make_room(const FillCtx &) {}
     __device__ __forceinline__ static int vcoord(const Axis &A, float t) {
         return A.zero ? A.zero_voxel() : A.voxel(A.locate(t, false));
     }
@@ -541,87 +642,55 @@ struct FillVis {
 // but does not evaluate, Sec. 2.3 and Fig. 1): in an empty voxel at distance d >= 2 from
 // every occupied voxel, the whole cube of voxels within d - 1 of it is empty,
 // so the ray leaves that cube in one step.  The cube's exit planes are the
-// current voxel's ray-order index plus d per axis; after the exit, the axes
-// it did not leave through are re-located exactly at the exit parameter
-// within the cube (the search the VDB walk uses on descent).  Occupied voxels
-// and empty ones at distance 1 are single cells, stepped as by the dense
-// march.
+// current voxel's plus d - 1 per axis; after the exit, the axes it did not
+// leave through are relocated exactly at the exit parameter within the cube.
+// Occupied voxels and empty ones at distance 1 are single cells, stepped as
+// by the dense march.  A cube may reach past the grid, where T goes on.
 struct DistCursor {
-    const uint32_t *bits;
-    const uint8_t *dist;
-    uint64_t level_base;   // index of the level's voxel (0,0,0)
+    const uint8_t *dist;   // the level's
     int R;
-    Axis A0, A1, A2;
-    int u0, u1, u2;        // ray-order voxel per moving axis
-    int v0, v1, v2;        // voxel index per axis
-    int k0, k1, k2;        // ray-order exit plane of the current cell per moving axis
-    float e0, e1, e2;      // their crossing parameters (+inf for zero axes)
-    int kx;                // exit plane of the axis exit() chose
-    int h;                 // the current cell reaches h voxels past the current voxel (0: a single voxel)
-    bool occ;
+    WalkAxis A0, A1, A2;
+    int w0, w1, w2;        // voxel in walk order
+    int p0, p1, p2;        // exit plane of the current cell
+    float t0, t1, t2;      // its crossing
+    int d;                 // the current voxel's distance (0: occupied)
+    float slack;           // relocate_slack
 
-    __device__ __forceinline__ void classify() {
-        const uint64_t idx = level_base + ((uint64_t)((uint32_t)v0 * (uint32_t)R + (uint32_t)v1) * (uint32_t)R + (uint32_t)v2);
-        const int d = dist[idx];
-        occ = d == 0;
-        h = d >= 2 ? d - 1 : 0;
+    __device__ __forceinline__ void lookup() {
+        const uint32_t v0 = (uint32_t)(w0 ^ A0.flip), v1 = (uint32_t)(w1 ^ A1.flip), v2 = (uint32_t)(w2 ^ A2.flip);
+        d = dist[(v0 * (uint32_t)R + v1) * (uint32_t)R + v2];
     }
-    // every axis computed, a zero axis's parameter replaced by +inf (cheaper
-    // than a per-axis branch)
-    __device__ __forceinline__ void exits_all() {
-        const float inf = __builtin_huge_valf();
-        k0 = min(u0 + h + 1, R);
-        k1 = min(u1 + h + 1, R);
-        k2 = min(u2 + h + 1, R);
-        e0 = A0.zero ? inf : A0.Tk(k0);
-        e1 = A1.zero ? inf : A1.Tk(k1);
-        e2 = A2.zero ? inf : A2.Tk(k2);
+    __device__ __forceinline__ uint32_t occupied() const { return d == 0 ? 1u : 0u; }
+    __device__ __forceinline__ float exit() {
+        const int n = max(d, 1);
+        p0 = w0 + n;
+        p1 = w1 + n;
+        p2 = w2 + n;
+        t0 = A0.T(p0);
+        t1 = A1.T(p1);
+        t2 = A2.T(p2);
+        return fminf(fminf(t0, t1), t2);
     }
-    __device__ __forceinline__ void enter() {
-        classify();
-        exits_all();
-    }
-    __device__ __forceinline__ bool occupied() const { return occ; }
-    __device__ __forceinline__ float exit(int &axis) {
-        float hi = e0;
-        int k = k0;
-        axis = 0;
-        if (e1 < hi) { hi = e1; k = k1; axis = 1; }
-        if (e2 < hi) { hi = e2; k = k2; axis = 2; }
-        kx = k;
-        return hi;
-    }
-    __device__ __forceinline__ bool step(int axis, float t) {
-        const int ka = kx;
-        if (ka >= R) return false;
-        const int h_old = h;
-        if (axis == 0) { u0 = ka; v0 = A0.voxel(ka); }
-        if (axis == 1) { u1 = ka; v1 = A1.voxel(ka); }
-        if (axis == 2) { u2 = ka; v2 = A2.voxel(ka); }
-        if (h_old > 0) {
-            // out of an empty cube: the other axes' voxels at t, inside the cube
-            if (axis != 0 && !A0.zero) { u0 = A0.advance_to(u0, t, k0 - 1); v0 = A0.voxel(u0); }
-            if (axis != 1 && !A1.zero) { u1 = A1.advance_to(u1, t, k1 - 1); v1 = A1.voxel(u1); }
-            if (axis != 2 && !A2.zero) { u2 = A2.advance_to(u2, t, k2 - 1); v2 = A2.voxel(u2); }
-        }
-        classify();
-        if (h_old == 0 && h == 0) {
-            // one voxel to the next: only the stepping axis's exit moves
-            if (axis == 0) { k0 = ka + 1; e0 = A0.Tk(k0); }
-            if (axis == 1) { k1 = ka + 1; e1 = A1.Tk(k1); }
-            if (axis == 2) { k2 = ka + 1; e2 = A2.Tk(k2); }
-        } else {
-            exits_all();
-        }
-        return true;
+    __device__ __forceinline__ void advance(float hi) {
+        w0 = t0 <= hi ? p0 : w0;
+        w1 = t1 <= hi ? p1 : w1;
+        w2 = t2 <= hi ? p2 : w2;
+        if (d > 1) relocate(A0, A1, A2, w0, w1, w2, p0, p1, p2, t0, t1, t2, hi, slack);
+        lookup();
     }
 };
 
 // ------------------------------------------------------------------ ray
 
 struct Ray {
-    float o0, o1, o2, d0, d1, d2, r0, r1, r2;
+    float o[3], d[3], r[3];
 };
+
+__device__ __forceinline__ Ray make_ray(const float o[3], const float d[3]) {
+    return Ray{{o[0], o[1], o[2]},
+               {d[0], d[1], d[2]},
+               {__fdiv_rn(1.0f, d[0]), __fdiv_rn(1.0f, d[1]), __fdiv_rn(1.0f, d[2])}};
+}
 
 // Traversals: 0 dense bitfield, 1 VDB tree with hierarchical steps, 2 dense
 // bitfield with chessboard distances (GridView::kind 0, 1, 2), 3 the VDB
@@ -651,79 +720,137 @@ struct CursorOf<4> {
 // Traversals that read the VDB tree.
 constexpr bool reads_tree(int kGrid) { return kGrid == 1 || kGrid == 3 || kGrid == 4; }
 
+// One level as a ray meets it: its axes and the parameters (E, X] it holds.
+struct RayLevel {
+    WalkAxis A[3];
+    float E, X;
+};
+
+// Entry and exit of the level box: the largest first and the smallest last
+// crossing of the moving axes; the others must hold o inside (floor rule).
+// False when the ray misses the level (or holds no parameter of it).
+__device__ __forceinline__ bool meet_level(const GridView &g, int lev, const Ray &ray, RayLevel &m) {
+    const float inf = __builtin_huge_valf();
+    m.E = -inf;
+    m.X = inf;
+    bool in = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const WalkAxis A = walk_axis(g.geom, lev, a, ray.o[a], ray.d[a], ray.r[a]);
+        const bool moves = axis_moves(ray.d[a], ray.r[a]);
+        const int first = A.flip & -g.R;   // walk-order planes first .. first + R
+        m.E = fmaxf(m.E, moves ? A.T(first) : -inf);
+        m.X = fminf(m.X, A.T(first + g.R));
+        const float P0 = __fadd_rn(A.B, 0.0f), PR = __fadd_rn(A.B, __fmul_rn((float)g.R, g.geom[12 * lev + 3 + a]));
+        in = in & (moves | ((P0 <= ray.o[a]) & (ray.o[a] < PR)));
+        m.A[a] = A;
+    }
+    return in & (m.E < m.X);
+}
+
+// Walk-order voxel owning t (inclusive = false) or the parameters just after
+// t (inclusive = true) on a moving axis: the largest w with T(w) < t (resp.
+// <=), first - 1 if none, first + R beyond the grid; from an estimate.
+__device__ __forceinline__ bool crossed(float T, float t, bool inclusive) { return (T < t) | (inclusive & (T == t)); }
+__device__ __forceinline__ int start_estimate(const WalkAxis &A, int first, int R, float t) {
+    const float q = floorf((t - A.T(first)) * A.per);
+    return first + (int)fminf(fmaxf(q, -1.0f), (float)R);   // a NaN becomes -1
+}
+__device__ __forceinline__ int start_exact(const WalkAxis &A, int w, int first, int R, float t, bool inclusive) {
+    while (w >= first && !crossed(A.T(w), t, inclusive)) --w;
+    while (w < first + R && crossed(A.T(w + 1), t, inclusive)) ++w;
+    return w;
+}
+// On an axis that does not move: the voxel holding o, P(v) <= o < P(v+1); -1
+// below the grid, R above it.
+__device__ __forceinline__ int start_still(float B, float h, float inv_h, int R, float o) {
+    const auto plane = [&](int v) { return __fadd_rn(B, __fmul_rn((float)v, h)); };
+    int v = (int)fminf(fmaxf(floorf((o - B) * inv_h), -1.0f), (float)R);
+    while (v >= 0 && plane(v) > o) --v;
+    while (v < R && plane(v + 1) <= o) ++v;
+    return v;
+}
+
 // Puts the cursor of level `lev` on the voxel owning t_min when t_min lies
 // after the segment start a, else on the voxel owning the parameters just
 // after a.  False when that voxel is outside the grid.
 template <int kGrid, class Vis>
 __device__ __forceinline__ bool cursor_begin(typename CursorOf<kGrid>::type &c, const GridView &g, const Tree &tree,
-                                             int lev, const Ray &ray, float a, const Lattice &lat, Vis &vis) {
+                                             int lev, const Ray &ray, const RayLevel &m, float a, const Lattice &lat,
+                                             Vis &vis) {
     const int R = g.R;
-    Axis A0 = load_axis(g.geom, lev, 0, R, ray.o0, ray.d0, ray.r0);
-    Axis A1 = load_axis(g.geom, lev, 1, R, ray.o1, ray.d1, ray.r1);
-    Axis A2 = load_axis(g.geom, lev, 2, R, ray.o2, ray.d2, ray.r2);
-    vis.begin_level(lev, A0, A1, A2);
+    vis.begin_level(g, lev, ray.o, ray.d);
     const bool after = lat.tmin > a;
     const float ts = after ? lat.tmin : a;
-    int u0 = A0.zero ? 0 : A0.locate(ts, !after);
-    int u1 = A1.zero ? 0 : A1.locate(ts, !after);
-    int u2 = A2.zero ? 0 : A2.locate(ts, !after);
-    int v0 = A0.zero ? A0.zero_voxel() : A0.voxel(u0);
-    int v1 = A1.zero ? A1.zero_voxel() : A1.voxel(u1);
-    int v2 = A2.zero ? A2.zero_voxel() : A2.voxel(u2);
-    if ((unsigned)v0 >= (unsigned)R || (unsigned)v1 >= (unsigned)R || (unsigned)v2 >= (unsigned)R) return false;
-    c.R = R;
-    c.A0 = A0; c.A1 = A1; c.A2 = A2;
-    c.u0 = u0; c.u1 = u1; c.u2 = u2;
-    c.v0 = v0; c.v1 = v1; c.v2 = v2;
+    int w[3];
+    bool sure = true;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int first = m.A[q].flip & -R;
+        w[q] = start_estimate(m.A[q], first, R, ts);
+        const bool moves = axis_moves(ray.d[q], ray.r[q]);
+        const bool enters = crossed(m.A[q].T(w[q]), ts, !after), leaves = crossed(m.A[q].T(w[q] + 1), ts, !after);
+        sure = sure & moves & enters & !leaves;
+    }
+    if (!sure) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            if (axis_moves(ray.d[q], ray.r[q]))
+                w[q] = start_exact(m.A[q], w[q], m.A[q].flip & -R, R, ts, !after);
+            else
+                w[q] = start_still(m.A[q].B, g.geom[12 * lev + 3 + q], g.geom[12 * lev + 6 + q], R, ray.o[q]);
+        }
+    }
+    bool in = true;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) in = in & ((uint32_t)(w[q] ^ m.A[q].flip) < (uint32_t)R);
+    if (!in) return false;
+    c.A0 = m.A[0];
+    c.A1 = m.A[1];
+    c.A2 = m.A[2];
     if constexpr (kGrid == 0) {
-        const float inf = __builtin_huge_valf();
-        c.bits = g.bits;
-        c.level_base = (uint64_t)lev * R * R * R;
-        c.tn0 = A0.zero ? inf : A0.Tk(u0 + 1);
-        c.tn1 = A1.zero ? inf : A1.Tk(u1 + 1);
-        c.tn2 = A2.zero ? inf : A2.Tk(u2 + 1);
+        c.start(g.bits, (uint64_t)lev * R * R * R, R, w[0], w[1], w[2]);
     } else if constexpr (kGrid == 2) {
-        c.bits = g.bits;
-        c.dist = g.dist;
-        c.level_base = (uint64_t)lev * R * R * R;
-        c.k0 = c.k1 = c.k2 = 0;
-        c.enter();
+        c.dist = g.dist + (uint64_t)lev * R * R * R;
+        c.R = R;
+        c.slack = relocate_slack(g.geom, lev, R, ray.o);
+        c.w0 = w[0];
+        c.w1 = w[1];
+        c.w2 = w[2];
+        c.lookup();
     } else {
         c.t = tree;
         c.lev = lev;
-        c.sh = 3 + tree.ilog2;
-        c.k0 = c.k1 = c.k2 = 0;
+        c.set_node(tree.root[tree.NR == 1 ? lev : 0]);   // of the level's only root cell, else set by the lookup
+        c.slack = relocate_slack(g.geom, lev, R, ray.o);
+        c.w0 = w[0];
+        c.w1 = w[1];
+        c.w2 = w[2];
+        c.Dm1 = 0;
         c.lblk = -1;
-        c.lbase = 0;
+        c.code = 0;
         c.lu4 = 0;
-        c.enter();
+        c.lookup(a);
     }
     return true;
 }
 
+// m: the level as the ray meets it (its axes are used, not its span)
 template <int kGrid, bool kSkip, class Vis, class Ctx>
-__device__ __forceinline__ void march_segment(const GridView &g, const Tree &tree, int lev, const Ray &ray, float a,
-                                              float b, const Lattice &lat, Vis &vis, const Ctx &ctx) {
+__device__ __forceinline__ void march_segment(const GridView &g, const Tree &tree, int lev, const Ray &ray,
+                                              const RayLevel &m, float a, float b, const Lattice &lat, Vis &vis,
+                                              const Ctx &ctx) {
     typename CursorOf<kGrid>::type c;
-    if (!cursor_begin<kGrid>(c, g, tree, lev, ray, a, lat, vis)) return;
+    if (!cursor_begin<kGrid>(c, g, tree, lev, ray, m, a, lat, vis)) return;
     drive<kSkip>(c, a, b, lat.tmax, vis, ctx);
 }
 
-// Level `lev` holds exactly the parameters (E, X]; false if the ray misses it.
-__device__ __forceinline__ bool span_of(const GridView &g, int lev, const Ray &ray, float &E, float &X) {
-    Axis A0 = load_axis(g.geom, lev, 0, g.R, ray.o0, ray.d0, ray.r0);
-    Axis A1 = load_axis(g.geom, lev, 1, g.R, ray.o1, ray.d1, ray.r1);
-    Axis A2 = load_axis(g.geom, lev, 2, g.R, ray.o2, ray.d2, ray.r2);
-    return level_span(A0, A1, A2, E, X);
-}
-
-// A single-level ray before its walk: the reciprocal direction and the
-// grid's span (E, X]; hit is false for a ray with no samples to find (it
-// misses the grid, the span lies outside [t_min, t_max], t_min > t_max, or
-// the origin or direction is not finite).
+// A single-level ray before its walk: hit is false for a ray with no samples
+// to find (it misses the grid, the span lies outside [t_min, t_max],
+// t_min > t_max, or the origin or direction is not finite).
 struct L1Span {
     Ray ray;
-    float E, X;
+    RayLevel m;
     bool hit;
 };
 
@@ -732,8 +859,8 @@ __device__ __forceinline__ L1Span l1_span(const GridView &g, const float o[3], c
     bool ok = lat.tmin <= lat.tmax;
 #pragma unroll
     for (int a = 0; a < 3; ++a) ok = ok && __builtin_isfinite(o[a]) && __builtin_isfinite(d[a]);
-    s.ray = Ray{o[0], o[1], o[2], d[0], d[1], d[2], __fdiv_rn(1.0f, d[0]), __fdiv_rn(1.0f, d[1]), __fdiv_rn(1.0f, d[2])};
-    s.hit = ok && span_of(g, 0, s.ray, s.E, s.X) && s.E < lat.tmax && s.X >= lat.tmin;
+    s.ray = make_ray(o, d);
+    s.hit = meet_level(g, 0, s.ray, s.m) & ok & (s.m.E < lat.tmax) & (s.m.X >= lat.tmin);
     return s;
 }
 
@@ -770,51 +897,33 @@ __device__ __forceinline__ void trace_ray(const GridView &g, const Tree &tree, c
                                           const Lattice &lat, Vis &vis, const Ctx &ctx) {
     if (kL1) {
         const L1Span s = l1_span(g, o, d, lat);
-        if (s.hit) march_segment<kGrid, kSkip>(g, tree, 0, s.ray, s.E, s.X, lat, vis, ctx);
+        if (s.hit) march_segment<kGrid, kSkip>(g, tree, 0, s.ray, s.m, s.m.E, s.m.X, lat, vis, ctx);
         return;
     }
     if (!(lat.tmin <= lat.tmax)) return;
 #pragma unroll
     for (int a = 0; a < 3; ++a)
         if (!__builtin_isfinite(o[a]) || !__builtin_isfinite(d[a])) return;
-    Ray ray{o[0], o[1], o[2], d[0], d[1], d[2], __fdiv_rn(1.0f, d[0]), __fdiv_rn(1.0f, d[1]), __fdiv_rn(1.0f, d[2])};
+    const Ray ray = make_ray(o, d);
     const int L = g.L;
     int f = -1;
     for (int lev = 0; lev < L && f < 0; ++lev) {
-        float E, X;
-        if (span_of(g, lev, ray, E, X)) f = lev;
+        RayLevel m;
+        if (meet_level(g, lev, ray, m)) f = lev;
     }
     if (f < 0) return;
     const int m = L - 1 - f;
     for (int k = 0; k <= 2 * m; ++k) {
         // the two levels whose spans bound segment k
-        int lev, inner;
-        if (k < m) {
-            lev = L - 1 - k;
-            inner = lev - 1;
-        } else if (k == m) {
-            lev = f;
-            inner = f;
-        } else {
-            lev = f + (k - m);
-            inner = lev - 1;
-        }
-        float E_l = 0.f, X_l = 0.f, E_i = 0.f, X_i = 0.f;
-        for (int q = 0; q < 2; ++q) {
-            float E, X;
-            span_of(g, q == 0 ? lev : inner, ray, E, X);
-            if (q == 0) {
-                E_l = E;
-                X_l = X;
-            } else {
-                E_i = E;
-                X_i = X;
-            }
-        }
-        float a = k <= m ? E_l : X_i;
-        float b = k < m ? E_i : X_l;
+        const int lev = k < m ? L - 1 - k : f + (k - m);
+        const int inner = k == m ? f : lev - 1;
+        RayLevel at, in;
+        meet_level(g, inner, ray, in);
+        meet_level(g, lev, ray, at);
+        const float a = k <= m ? at.E : in.X;
+        const float b = k < m ? in.E : at.X;
         if (a >= lat.tmax) break;   // this and every later segment lie past t_max
-        if (a < b && b >= lat.tmin) march_segment<kGrid, kSkip>(g, tree, lev, ray, a, b, lat, vis, ctx);
+        if (a < b && b >= lat.tmin) march_segment<kGrid, kSkip>(g, tree, lev, ray, at, a, b, lat, vis, ctx);
     }
 }
 
