@@ -87,14 +87,25 @@ constexpr int count_waves_per_eu(int kGrid, bool kSkip, bool kL1) {
     OGV_COUNT_SKIP(3, false, true) OGV_COUNT_SKIP(3, false, false) OGV_COUNT_SKIP(4, true, true)               \
     OGV_COUNT_SKIP(4, true, false) OGV_COUNT_SKIP(4, false, true) OGV_COUNT_SKIP(4, false, false)
 
+// The rows of the workspace a call keeps per ray (2^parts_log2, one per part
+// in t order), and how many bits of a ray's part number vary across
+// neighbouring lanes (ray_of_thread).
+struct RowMap {
+    int parts_log2, lane_log2;
+};
+
 template <int kGrid, bool kSkip, bool kLds, bool kL1>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(count_waves_per_eu(kGrid, kSkip, kL1))))
 count_kernel(GridView g, const float *__restrict__ origins, const float *__restrict__ dirs, int64_t n_rays,
              Lattice lat, int32_t *__restrict__ counts, int32_t *__restrict__ nruns, RunPool pool, int image_width,
-             int64_t *__restrict__ tile_sums, int64_t *__restrict__ chunk_sums) {
+             RowMap rows, int64_t *__restrict__ tile_sums, int64_t *__restrict__ chunk_sums) {
     extern __shared__ __align__(16) uint32_t smem[];
     Tree tree = reads_tree(kGrid) ? load_tree<kLds>(g, smem) : Tree{};
-    const int64_t i = ray_of_thread((int64_t)blockIdx.x * kBlock + threadIdx.x, n_rays, image_width);
+    // ray i, and the row its part's counts and runs are kept in
+    RayPart part;
+    const int64_t i = ray_of_thread((int64_t)blockIdx.x * kBlock + threadIdx.x, n_rays, image_width, rows.parts_log2,
+                                    rows.lane_log2, part);
+    const int64_t row = i < 0 ? -1 : (i << rows.parts_log2) + part.j;
     int32_t n = 0;
     if constexpr (kL1) {
         // the span first, so the wave's priority can follow its longest ray
@@ -110,27 +121,27 @@ count_kernel(GridView g, const float *__restrict__ origins, const float *__restr
                           g.R);
         if (i >= 0) {
             const CountCtx ctx{lat, pool};
-            CountVis vis = make_count_vis(i, pool);
-            if (s.hit) march_segment<kGrid, kSkip>(g, tree, 0, s.ray, s.m, s.m.E, s.m.X, lat, vis, ctx);
+            CountVis vis = make_count_vis(row, pool);
+            if (s.hit) march_l1<kGrid, kSkip>(g, tree, s, part, lat, vis, ctx);
             vis.finish(ctx);
             n = vis.n;
-            counts[i] = n;
-            nruns[i] = vis.nr;
+            counts[row] = n;
+            nruns[row] = vis.nr;
         }
     } else if (i >= 0) {
         float o[3], d[3];
         load_ray(origins, dirs, i, o, d);
         const CountCtx ctx{lat, pool};
-        CountVis vis = make_count_vis(i, pool);
-        trace_ray<kGrid, kSkip, kL1>(g, tree, o, d, lat, vis, ctx);
+        CountVis vis = make_count_vis(row, pool);
+        trace_ray<kGrid, kSkip, kL1>(g, tree, o, d, part, lat, vis, ctx);
         vis.finish(ctx);
         n = vis.n;
-        counts[i] = n;
-        nruns[i] = vis.nr;
+        counts[row] = n;
+        nruns[row] = vis.nr;
     }
     static_assert(kScanTile == 1 << 12 && kBlock == 1 << 8, "group sums assume 4096-ray tiles, 256-ray chunks");
-    add_group_sums<12>(i, n, tile_sums);
-    add_chunk_sums(i, n, chunk_sums);
+    add_group_sums<12>(row, n, tile_sums);
+    add_chunk_sums(row, n, chunk_sums);
 }
 
 }  // namespace ogv

@@ -8,10 +8,10 @@
 
 namespace ogv {
 
-#define OGV_COUNT_SKIP(V, L, L1)                                                                        \
-    template __global__ void count_kernel<V, true, L, L1>(GridView, const float *, const float *, int64_t, \
-                                                          Lattice, int32_t *, int32_t *, RunPool, int,  \
-                                                          int64_t *, int64_t *);
+#define OGV_COUNT_SKIP(V, L, L1)                                                                               \
+    template __global__ void count_kernel<V, true, L, L1>(GridView, const float *, const float *, int64_t, Lattice, \
+                                                          int32_t *, int32_t *, RunPool, int, RowMap, int64_t *,    \
+                                                          int64_t *);
 OGV_COUNT_SKIP_ALL
 #undef OGV_COUNT_SKIP
 

@@ -10,6 +10,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -29,7 +30,7 @@ namespace ogv {
 #define OGV_COUNT_SKIP(V, L, L1)                                                                               \
     extern template __global__ void count_kernel<V, true, L, L1>(GridView, const float *, const float *, int64_t, \
                                                                  Lattice, int32_t *, int32_t *, RunPool, int,  \
-                                                                 int64_t *, int64_t *);
+                                                                 RowMap, int64_t *, int64_t *);
 OGV_COUNT_SKIP_ALL
 #undef OGV_COUNT_SKIP
 
@@ -55,7 +56,7 @@ __global__ void __launch_bounds__(kBlock) fill_kernel(GridView g, const float *_
         vis.idx = first;
         vis.ray = (int32_t)i;
         vis.lev = 0;
-        trace_ray<kGrid, kSkip>(g, tree, o, d, lat, vis, ctx);
+        trace_ray<kGrid, kSkip>(g, tree, o, d, RayPart{0, 1}, lat, vis, ctx);
     }
 }
 
@@ -97,16 +98,19 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kEx
     const Tree tree = reads_tree(kGrid) ? load_tree<false>(g, nullptr) : Tree{};
     const FillCtx ctx{lat, capacity, ray_ids, t0, t1, nullptr, g.R};
     for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < m; k += (int64_t)gridDim.x * kBlock) {
-        const int64_t i = lost[k];
-        const int64_t first = kScan ? offset_of_ray(i, cs) : offsets[i];
+        const int64_t row = lost[k];
+        const int64_t first = kScan ? offset_of_ray(row, cs) : offsets[row];
         if (first >= capacity) continue;
+        const int sh = kScan ? cs.parts_log2 : 0;
+        const int64_t i = row >> sh;
         float o[3], d[3];
         load_ray(origins, dirs, i, o, d);
         FillVis<false> vis;
         vis.idx = first;
         vis.ray = (int32_t)i;
         vis.lev = 0;
-        trace_ray<kGrid, kSkip>(g, tree, o, d, lat, vis, ctx);
+        const RayPart part{(int)(row & ((1 << sh) - 1)), 1 << sh};
+        trace_ray<kGrid, kSkip>(g, tree, o, d, part, lat, vis, ctx);
     }
 }
 
@@ -269,8 +273,37 @@ ogv_status validate_sampling(const ogv_grid *grid, int32_t variant, const float 
 
 namespace {
 
+// A call with few rays walks each ray in parts, a lane each, whose counts and
+// runs are rows of the workspace (2^parts_log2 rows a ray, in t order).  Such
+// a call does not fill the chip: its time is the longest wave's chain of
+// steps, about 0.5 us each, which n parts cut by n.  More parts than that
+// need more starts, rows and cut runs than they save.  The number depends on
+// the rays alone, as the scan call knows nothing else.  Walks of a 128^3 grid
+// measured with the rule's parts, against one lane a ray (and against twice
+// the parts): 4,096 rays 16 against 61 us, 16,384 27 against 102,
+// 65,536 50 against 94 (46, but the expansion loses more), 90,000 54 against
+// 101 (53), 160,000 72 against 101 (72).  Beyond 262,144 rays two parts still
+// save 5% on one level and cost 25% on cascades.
+int parts_log2_of(int64_t n_rays) {
+    return n_rays <= 16384 ? 4 : n_rays <= 32768 ? 3 : n_rays <= 131072 ? 2 : n_rays <= 262144 ? 1 : 0;
+}
+
+// Over one level the parts of a ray sit in neighbouring lanes: their rows are
+// then written together (a 64x64 frame 25 us against 32 with the parts in
+// different waves, 128x128 39 against 77).  Over cascades neighbouring lanes
+// would march different levels, each with its own length of search for its
+// first segment, so only a quarter of a ray's parts are neighbours (128x128
+// frame 68 us, against 100 with none and 70 with half; 256x256, four parts,
+// 98 with none against 107 with half), and none where the rows stay in L2
+// anyway (64x64 51 against 57).
+RowMap row_map(int64_t n_rays, int parts_log2, int levels) {
+    if (levels == 1) return RowMap{parts_log2, parts_log2};
+    return RowMap{parts_log2, n_rays <= 8192 ? 0 : std::max(parts_log2 - 2, 0)};
+}
+
 struct Plan {
-    int64_t n_rays;
+    int64_t n_rays;   // rows: rays << parts_log2
+    int parts_log2;
     size_t off_counts, off_nruns, off_runs, off_next, off_chunks, off_cnext, off_lost, off_tiles, off_csums, off_tab,
         off_ntab, off_thdr,
         total;
@@ -279,7 +312,9 @@ struct Plan {
     int32_t tab_cap;
 };
 
-bool make_plan(int64_t n_rays, float near_t, float far_t, const ogv_step *step, Plan *p, std::string *why) {
+bool make_plan(int64_t rays, float near_t, float far_t, const ogv_step *step, Plan *p, std::string *why) {
+    p->parts_log2 = parts_log2_of(rays);
+    const int64_t n_rays = rays << p->parts_log2;
     p->n_rays = n_rays;
     p->n_tiles = scan_tiles(n_rays);
     p->tab_cap = cone_table_capacity(near_t, far_t, step);
@@ -329,6 +364,8 @@ constexpr size_t kLdsTreeBytes = 32768;
 
 
 struct Bufs {
+    int64_t rows;
+    int parts_log2;
     int32_t *counts, *nruns;
     RunPool pool;
     int64_t *tiles;
@@ -338,6 +375,8 @@ struct Bufs {
 Bufs bufs_of(void *ws, const Plan &p) {
     char *w = (char *)ws;
     Bufs b;
+    b.rows = p.n_rays;
+    b.parts_log2 = p.parts_log2;
     b.counts = (int32_t *)(w + p.off_counts);
     b.nruns = (int32_t *)(w + p.off_nruns);
     b.pool.slots = (int2 *)(w + p.off_runs);
@@ -362,17 +401,18 @@ RunReader reader_of(const Bufs &b) {
 template <int kGrid, bool kSkip, bool kLds>
 void launch_count(const GridView &g, const float *o, const float *d, int64_t n, const Lattice &lat, const Bufs &b,
                   int width, hipStream_t s) {
-    unsigned blocks = (unsigned)((tiled_threads(n, width) + kBlock - 1) / kBlock);
+    unsigned blocks = (unsigned)((tiled_threads(n, width, b.parts_log2) + kBlock - 1) / kBlock);
     size_t shm = kLds ? lds_bytes(g) : 0;
-    const int64_t nt = scan_tiles(n), nc = (n + kBlock - 1) / kBlock;
+    const RowMap rows = row_map(n, b.parts_log2, g.L);
+    const int64_t nt = scan_tiles(b.rows), nc = (b.rows + kBlock - 1) / kBlock;
     pool_reset_kernel<<<(unsigned)std::min<int64_t>((nc + 255) / 256 + 1, 64), 256, 0, s>>>(b.pool.head, b.tiles, nt,
                                                                                          b.csums, nc);
     if (g.L == 1)
         count_kernel<kGrid, kSkip, kLds, true>
-            <<<blocks, kBlock, shm, s>>>(g, o, d, n, lat, b.counts, b.nruns, b.pool, width, b.tiles, b.csums);
+            <<<blocks, kBlock, shm, s>>>(g, o, d, n, lat, b.counts, b.nruns, b.pool, width, rows, b.tiles, b.csums);
     else
         count_kernel<kGrid, kSkip, kLds, false>
-            <<<blocks, kBlock, shm, s>>>(g, o, d, n, lat, b.counts, b.nruns, b.pool, width, b.tiles, b.csums);
+            <<<blocks, kBlock, shm, s>>>(g, o, d, n, lat, b.counts, b.nruns, b.pool, width, rows, b.tiles, b.csums);
 }
 
 template <int kGrid, bool kSkip, bool kLds>
@@ -466,7 +506,37 @@ ogv_status count_and_scan(const ogv_grid *grid, int32_t variant, int width, cons
     Bufs b = bufs_of(ws, p);
     dispatch_count(grid->view, variant, o, d, n, lat, b, width, s);
     OGV_CHECK_LAUNCH();
-    OGV_CHECK_HIP(launch_excl_scan_from_sums(b.counts, n, offsets, b.tiles, capacity, overflow, s));
+    OGV_CHECK_HIP(launch_excl_scan_from_sums(b.counts, b.rows, offsets, b.tiles, capacity, overflow, s, b.parts_log2));
+    return OGV_OK;
+}
+
+// The expansion of the runs the count pass left in the workspace.  scan: the
+// rows' offsets come from the count pass's counts and sums, and write says
+// whether the offsets array and the overflow flag are written; else they are
+// read from the offsets array.
+ogv_status expand(const ogv_grid *grid, int32_t variant, const float *o, const float *d, int64_t *offsets, bool scan,
+                  bool write, int64_t cap, int32_t *ids, float *t0, float *t1, int32_t *overflow, const Lattice &lat,
+                  const Bufs &b, hipStream_t s) {
+    const unsigned blocks = (unsigned)min(expand_items(b.rows), (int64_t)INT32_MAX);
+    const int vec4 = (((uintptr_t)ids | (uintptr_t)t0 | (uintptr_t)t1) & 15) == 0;
+    const GridView &g = grid->view;
+    const ChunkScan cs = scan ? ChunkScan{b.counts, b.tiles, b.csums, overflow, b.parts_log2, write ? 1 : 0} : ChunkScan{};
+    // the expansion's lost-ray walk reads the tree from global memory (the
+    // LDS flag is ignored)
+#define OGV_LAUNCH(V, K, L)                                                                                          \
+    do {                                                                                                             \
+        if (scan)                                                                                                    \
+            expand_kernel<V, K, true><<<blocks, kBlock, 0, s>>>(g, o, d, offsets, cs, b.rows, b.nruns, reader_of(b), \
+                                                                lat, cap, ids, t0, t1, vec4, b.pool.lost,            \
+                                                                b.pool.n_lost);                                      \
+        else                                                                                                         \
+            expand_kernel<V, K, false><<<blocks, kBlock, 0, s>>>(g, o, d, offsets, cs, b.rows, b.nruns,              \
+                                                                 reader_of(b), lat, cap, ids, t0, t1, vec4,          \
+                                                                 b.pool.lost, b.pool.n_lost);                        \
+    } while (0)
+    OGV_DISPATCH(g, variant);
+#undef OGV_LAUNCH
+    OGV_CHECK_LAUNCH();
     return OGV_OK;
 }
 
@@ -483,19 +553,8 @@ ogv_status fill_all(const ogv_grid *grid, int32_t variant, const float *o, const
         OGV_CHECK_LAUNCH();
         return OGV_OK;
     }
-    const unsigned blocks = (unsigned)min(expand_items(n), (int64_t)INT32_MAX);
-    const int vec4 = (((uintptr_t)ids | (uintptr_t)t0 | (uintptr_t)t1) & 15) == 0;
-    const GridView &g = grid->view;
-    // the expansion's lost-ray walk reads the tree from global memory (the
-    // LDS flag is ignored)
-#define OGV_LAUNCH(V, K, L)                                                                                          \
-    expand_kernel<V, K, false><<<blocks, kBlock, 0, s>>>(g, o, d, const_cast<int64_t *>(offsets), ChunkScan{}, n,    \
-                                                          b.nruns, reader_of(b), lat, cap, ids, t0, t1, vec4,        \
-                                                          b.pool.lost, b.pool.n_lost)
-    OGV_DISPATCH(g, variant);
-#undef OGV_LAUNCH
-    OGV_CHECK_LAUNCH();
-    return OGV_OK;
+    return expand(grid, variant, o, d, const_cast<int64_t *>(offsets), b.parts_log2 > 0, false, cap, ids, t0, t1, nullptr,
+                  lat, b, s);
 }
 
 // Rays a one-call pass scans inside the expansion: each expansion block sums
@@ -504,25 +563,6 @@ ogv_status fill_all(const ogv_grid *grid, int32_t variant, const float *o, const
 // 640,000-ray object workload, 157 tiles, 0.271 -> 0.264 ms a step; the
 // 1,064,960-ray cascades, 260 tiles, 0.503 -> 0.510 ms).
 constexpr int64_t kScanInExpandTiles = 192;
-
-// scan and fill of a one-call pass in one launch: the expansion writes the
-// offsets (and the overflow flag) itself from the count pass's sums
-ogv_status scan_fill_fused(const ogv_grid *grid, int32_t variant, const float *o, const float *d, int64_t n,
-                           const Lattice &lat, int64_t *offsets, int64_t cap, int32_t *ids, float *t0, float *t1,
-                           int32_t *overflow, void *ws, const Plan &p, hipStream_t s) {
-    Bufs b = bufs_of(ws, p);
-    const unsigned blocks = (unsigned)min(expand_items(n), (int64_t)INT32_MAX);
-    const int vec4 = (((uintptr_t)ids | (uintptr_t)t0 | (uintptr_t)t1) & 15) == 0;
-    const GridView &g = grid->view;
-    const ChunkScan cs{b.counts, b.tiles, b.csums, overflow};
-#define OGV_LAUNCH(V, K, L)                                                                                          \
-    expand_kernel<V, K, true><<<blocks, kBlock, 0, s>>>(g, o, d, offsets, cs, n, b.nruns, reader_of(b), lat, cap,    \
-                                                         ids, t0, t1, vec4, b.pool.lost, b.pool.n_lost)
-    OGV_DISPATCH(g, variant);
-#undef OGV_LAUNCH
-    OGV_CHECK_LAUNCH();
-    return OGV_OK;
-}
 
 // Voxel ids are int32: every id of the grid, ((l*R+i)*R+j)*R+k, must fit.
 ogv_status check_voxel_ids(const ogv_grid *grid, const int32_t *vox, const char *fn) {
@@ -609,7 +649,7 @@ extern "C" ogv_status ogv_sample_scan(int64_t n, int64_t *offsets, void *ws, siz
         return OGV_OK;
     }
     Bufs b = bufs_of(ws, p);
-    OGV_CHECK_HIP(launch_excl_scan_from_sums(b.counts, n, offsets, b.tiles, 0, nullptr, s));
+    OGV_CHECK_HIP(launch_excl_scan_from_sums(b.counts, b.rows, offsets, b.tiles, 0, nullptr, s, b.parts_log2));
     return OGV_OK;
 }
 
@@ -649,8 +689,8 @@ extern "C" ogv_status ogv_sample_rays(const ogv_grid *grid, const ogv_sample_opt
         // walk, then one launch that scans and fills
         dispatch_count(grid->view, opts.variant, o, d, n, lat, bufs_of(ws, p), opts.image_width, s);
         OGV_CHECK_LAUNCH();
-        return scan_fill_fused(grid, opts.variant, o, d, n, lat, offsets, capacity, ray_ids, t0, t1, overflow, ws, p,
-                               s);
+        return expand(grid, opts.variant, o, d, offsets, true, true, capacity, ray_ids, t0, t1, overflow, lat,
+                      bufs_of(ws, p), s);
     }
     if ((st = count_and_scan(grid, opts.variant, opts.image_width, o, d, n, lat, offsets, ws, p, capacity, overflow,
                              s)) != OGV_OK)

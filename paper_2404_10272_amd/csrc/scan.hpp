@@ -111,7 +111,8 @@ __global__ void __launch_bounds__(kScanThreads) scan_apply_kernel(const int32_t 
 
 // Apply with the tile's base summed in place from the raw tile sums (no
 // separate scan of the tile sums); the last tile also writes the total and
-// the overflow flag.  For up to kScanDirectTiles tiles.
+// the overflow flag.  For up to kScanDirectTiles tiles.  Only every
+// 2^every_log2-th entry of the scan is kept (n is a multiple of that).
 constexpr int64_t kScanDirectTiles = 4096;
 
 __global__ void __launch_bounds__(kScanThreads) scan_apply_direct_kernel(const int32_t *__restrict__ counts, int64_t n,
@@ -119,7 +120,7 @@ __global__ void __launch_bounds__(kScanThreads) scan_apply_direct_kernel(const i
                                                                         int64_t *__restrict__ offsets,
                                                                         int64_t capacity,
                                                                         int32_t *__restrict__ overflow,
-                                                                        const int32_t *gate = nullptr) {
+                                                                        const int32_t *gate = nullptr, int every_log2 = 0) {
     __shared__ int64_t lds[kScanThreads / 64];
     if (gate && *gate == 0) return;
     int64_t before = 0;
@@ -140,11 +141,11 @@ __global__ void __launch_bounds__(kScanThreads) scan_apply_direct_kernel(const i
 #pragma unroll
     for (int j = 0; j < kScanItems; ++j) {
         const int64_t i = base + j;
-        if (i < n) offsets[i] = ex;
+        if (i < n && (i & (((int64_t)1 << every_log2) - 1)) == 0) offsets[i >> every_log2] = ex;
         ex += c[j];
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        offsets[n] = tile_base + total;
+        offsets[n >> every_log2] = tile_base + total;
         if (overflow) *overflow = tile_base + total > capacity ? 1 : 0;
     }
 }
@@ -172,12 +173,14 @@ inline hipError_t launch_excl_scan(const int32_t *in, int64_t n, int64_t *out, i
 // As launch_excl_scan, for a producer that has already left each tile's sum
 // of `in` in tiles[0 .. scan_tiles(n)-1]: up to kScanDirectTiles tiles one
 // apply launch reads them (and leaves them intact, so the scan can be
-// repeated); longer inputs take the full three launches.
+// repeated); longer inputs take the full three launches (every_log2 is 0
+// for them: only small calls keep more rows than rays).
 inline hipError_t launch_excl_scan_from_sums(const int32_t *in, int64_t n, int64_t *out, int64_t *tiles,
-                                             int64_t capacity, int32_t *overflow, hipStream_t s) {
+                                             int64_t capacity, int32_t *overflow, hipStream_t s, int every_log2) {
     int64_t nt = scan_tiles(n);
     if (nt > 0 && nt <= kScanDirectTiles) {
-        scan_apply_direct_kernel<<<(unsigned)nt, kScanThreads, 0, s>>>(in, n, tiles, out, capacity, overflow);
+        scan_apply_direct_kernel<<<(unsigned)nt, kScanThreads, 0, s>>>(in, n, tiles, out, capacity, overflow, nullptr,
+                                                                       every_log2);
         return hipGetLastError();
     }
     return launch_excl_scan(in, n, out, tiles, capacity, overflow, s);

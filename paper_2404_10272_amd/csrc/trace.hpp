@@ -884,20 +884,47 @@ __device__ __forceinline__ void set_wave_priority(float nv, int R) {
     else if (lvl == 1) __builtin_amdgcn_s_setprio(1);
 }
 
-// All samples of one ray, in increasing t.  The cascade boxes are nested
-// (checked when the grid is built), so level l holds exactly (E_l, X_l] and
-// these intervals nest.  With f the finest level the ray meets and
-// m = L-1-f, segment k = 0..2m runs in t order: for k < m level L-1-k on
+// A ray may be walked in parts, each by a lane of its own, that meet at
+// parameters between its first and last: part j of n holds (c_j, c_{j+1}]
+// with c_0 = -inf and c_n = +inf, and walks as if the ray began after c_j.
+// Parts of one ray compute a shared c from the same inputs with the same
+// operations, so they agree on it to the bit, and every parameter belongs to
+// exactly one part.
+struct RayPart {
+    int j, n;
+};
+
+// All samples of one part of a ray, in increasing t.  The cascade boxes are
+// nested (checked when the grid is built), so level l holds exactly
+// (E_l, X_l] and these intervals nest.  With f the finest level the ray meets
+// and m = L-1-f, segment k = 0..2m runs in t order: for k < m level L-1-k on
 // (E_{L-1-k}, E_{L-2-k}]; for k = m level f on (E_f, X_f]; for k > m level
 // f+(k-m) on (X_{f+k-m-1}, X_{f+k-m}].  Each segment is marched by its level.
 // kL1: the grid has a single level (no cascades), so the level geometry is
 // uniform across the wave.
+//
+// The parts share a ray's range evenly by the voxels it crosses: over one
+// level evenly in t, over cascades by length over voxel size.
+template <int kGrid, bool kSkip, class Vis, class Ctx>
+__device__ __forceinline__ void march_l1(const GridView &g, const Tree &tree, const L1Span &s, RayPart part,
+                                         const Lattice &lat, Vis &vis, const Ctx &ctx) {
+    float a = s.m.E, b = s.m.X;
+    if (part.n > 1) {
+        const float t0 = fmaxf(a, lat.tmin), len = __fsub_rn(fminf(b, lat.tmax), t0), each = 1.0f / (float)part.n;
+        const auto c = [&](int j) { return __fadd_rn(t0, __fmul_rn(len, __fmul_rn((float)j, each))); };
+        if (part.j > 0) a = fmaxf(a, c(part.j));
+        if (part.j + 1 < part.n) b = fminf(b, c(part.j + 1));
+        if (!(a < b)) return;
+    }
+    march_segment<kGrid, kSkip>(g, tree, 0, s.ray, s.m, a, b, lat, vis, ctx);
+}
+
 template <int kGrid, bool kSkip, bool kL1 = false, class Vis, class Ctx>
 __device__ __forceinline__ void trace_ray(const GridView &g, const Tree &tree, const float o[3], const float d[3],
-                                          const Lattice &lat, Vis &vis, const Ctx &ctx) {
+                                          RayPart part, const Lattice &lat, Vis &vis, const Ctx &ctx) {
     if (kL1) {
         const L1Span s = l1_span(g, o, d, lat);
-        if (s.hit) march_segment<kGrid, kSkip>(g, tree, 0, s.ray, s.m, s.m.E, s.m.X, lat, vis, ctx);
+        if (s.hit) march_l1<kGrid, kSkip>(g, tree, s, part, lat, vis, ctx);
         return;
     }
     if (!(lat.tmin <= lat.tmax)) return;
@@ -906,24 +933,59 @@ __device__ __forceinline__ void trace_ray(const GridView &g, const Tree &tree, c
         if (!__builtin_isfinite(o[a]) || !__builtin_isfinite(d[a])) return;
     const Ray ray = make_ray(o, d);
     const int L = g.L;
+    const auto clip = [&](float t) { return fminf(fmaxf(t, lat.tmin), lat.tmax); };
+    // voxels of level lev per unit of t, up to a factor the levels share
+    const auto density = [&](int lev) { return g.geom[12 * lev + 6]; };
     int f = -1;
-    for (int lev = 0; lev < L && f < 0; ++lev) {
+    float work = 0.0f;    // the ray's range in voxels (parts only)
+    float inner_len = 0.0f;
+    for (int lev = 0; lev < L && (f < 0 || part.n > 1); ++lev) {
         RayLevel m;
-        if (meet_level(g, lev, ray, m)) f = lev;
+        if (meet_level(g, lev, ray, m)) {
+            if (f < 0) f = lev;
+            const float len = clip(m.X) - clip(m.E);
+            work += fmaxf(len - inner_len, 0.0f) * density(lev);
+            inner_len = len;
+        }
     }
     if (f < 0) return;
+    const float each = work / (float)part.n;
+    const float from = __fmul_rn((float)part.j, each), to = __fmul_rn((float)(part.j + 1), each);
+    float done = 0.0f;    // voxels before the segment
     const int m = L - 1 - f;
-    for (int k = 0; k <= 2 * m; ++k) {
-        // the two levels whose spans bound segment k
-        const int lev = k < m ? L - 1 - k : f + (k - m);
-        const int inner = k == m ? f : lev - 1;
-        RayLevel at, in;
-        meet_level(g, inner, ray, in);
-        meet_level(g, lev, ray, at);
-        const float a = k <= m ? at.E : in.X;
-        const float b = k < m ? in.E : at.X;
-        if (a >= lat.tmax) break;   // this and every later segment lie past t_max
-        if (a < b && b >= lat.tmin) march_segment<kGrid, kSkip>(g, tree, lev, ray, at, a, b, lat, vis, ctx);
+    // Every lane first passes the segments it has nothing to do in, then
+    // marches: the lanes of a wave (parts of a ray, or rays that enter
+    // through different levels) march their own segments side by side.
+    for (int k = 0; k <= 2 * m;) {
+        RayLevel at;
+        int lev = 0;
+        float a = 0.0f, b = 0.0f;
+        bool found = false;
+        for (; k <= 2 * m && !found; ++k) {
+            // the two levels whose spans bound segment k
+            lev = k < m ? L - 1 - k : f + (k - m);
+            RayLevel in;
+            meet_level(g, k == m ? f : lev - 1, ray, in);
+            meet_level(g, lev, ray, at);
+            a = k <= m ? at.E : in.X;
+            b = k < m ? in.E : at.X;
+            bool starts = true;
+            if (part.n > 1) {
+                const float t0 = clip(a), len = __fsub_rn(clip(b), t0), here = __fmul_rn(len, density(lev));
+                const float before = done, next = __fadd_rn(done, here);
+                const auto c = [&](float w) {
+                    return fminf(fmaxf(__fadd_rn(t0, __fmul_rn(len, (w - before) / here)), a), b);
+                };
+                const bool last = part.j + 1 == part.n;
+                starts = (part.j == 0 || from < next) && (last || to > before);
+                const float a_part = part.j > 0 && from > before ? c(from) : a;
+                b = !last && to < next ? c(to) : b;
+                a = a_part;
+                done = next;
+            }
+            found = starts && a < b && b >= lat.tmin && a < lat.tmax;
+        }
+        if (found) march_segment<kGrid, kSkip>(g, tree, lev, ray, at, a, b, lat, vis, ctx);
     }
 }
 
@@ -1021,17 +1083,20 @@ __device__ __forceinline__ int64_t block_incl_scan256(int64_t x, int64_t *lds, i
     return base + x;   // inclusive
 }
 
-// The scan done inside the expansion (one-call sampling): every block derives
-// its 256-ray chunk's offsets from the count pass's per-ray counts and its
+// The scan done inside the expansion (one-call sampling, and rays walked in
+// parts, whose rows the offsets array does not list): every block derives
+// its 256-row chunk's offsets from the count pass's per-ray counts and its
 // sums per 4096-ray scan tile and per 256-ray chunk, and the first part of
 // every chunk writes them to the offsets array (the last chunk also the total
 // and the overflow flag).  counts == nullptr: the offsets array is read.
 constexpr int kChunksPerTile = kScanTile / kBlock;
 struct ChunkScan {
-    const int32_t *counts;       // [n_rays]
+    const int32_t *counts;       // [n_rays] (rows)
     const int64_t *tile_sums;    // [ceil(n_rays / kScanTile)]
     const int64_t *chunk_sums;   // [ceil(n_rays / kBlock)]
     int32_t *overflow;           // nullable: set to (total > capacity)
+    int32_t parts_log2;          // log2 of a ray's rows: the rows of ray i are i << parts_log2 ...
+    int32_t write;               // 0: the offsets array is not written (it already holds them)
 };
 
 // First output of ray i from the sums (for the rare rays the count pass could
@@ -1130,10 +1195,10 @@ __device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float2 *s_lat,
         off = base + incl - cnt;
         off_next = base + incl;
         bend = base + total;
-        if (part == 0) {
-            if (in) offsets[r] = off;
+        if (part == 0 && cs.write != 0) {
+            if (in && (r & ((1 << cs.parts_log2) - 1)) == 0) offsets[r >> cs.parts_log2] = off;
             if (r0 + kBlock >= n_rays && threadIdx.x == 0) {
-                offsets[n_rays] = bend;
+                offsets[n_rays >> cs.parts_log2] = bend;
                 if (cs.overflow) *cs.overflow = bend > capacity ? 1 : 0;
             }
         }
@@ -1214,7 +1279,7 @@ __device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float2 *s_lat,
             if (idx >= 0 && idx <= cn) s_start[idx] = st;
             if (idx >= 0 && idx < cn) {
                 s_bn[idx] = (uint32_t)rn.x - st;
-                s_ray[idx] = lost ? -1 : (int32_t)r;
+                s_ray[idx] = lost ? -1 : (int32_t)(kScan ? r >> cs.parts_log2 : r);
                 s_scene[idx] = (int16_t)scene;
             }
             st += (uint32_t)(rn.y - rn.x);
@@ -1364,11 +1429,12 @@ __device__ __forceinline__ void expand_block(int64_t *__restrict__ offsets, cons
 
 // ------------------------------------------------------------------ ray order
 
-// Threads per image-tiled launch: 8x8-pixel tiles of 64 lanes (one wave).
-__host__ __device__ inline int64_t tiled_threads(int64_t n, int width) {
-    if (width <= 0) return n;
+// Threads per image-tiled launch: 8x8-pixel tiles of 64 lanes (one wave);
+// with rays walked in parts, 2^parts_log2 threads a ray.
+__host__ __device__ inline int64_t tiled_threads(int64_t n, int width, int parts_log2 = 0) {
+    if (width <= 0) return ((n + 63) / 64 * 64) << parts_log2;
     const int64_t rows = (n + width - 1) / width;
-    return ((width + 7) / 8) * ((rows + 7) / 8) * (int64_t)64;
+    return (((width + 7) / 8) * ((rows + 7) / 8) * (int64_t)64) << parts_log2;
 }
 
 // Ray walked by thread t: t itself, or with an image of `width` pixels per
@@ -1384,6 +1450,20 @@ __device__ __forceinline__ int64_t ray_of_thread(int64_t t, int64_t n, int width
     if (px >= width) return -1;
     const int64_t r = py * width + px;
     return r < n ? r : -1;
+}
+
+// The same with rays walked in parts: the lowest lane_log2 bits of a ray's
+// part number vary across neighbouring lanes, the others across waves.
+__device__ __forceinline__ int64_t ray_of_thread(int64_t t, int64_t n, int width, int parts_log2, int lane_log2,
+                                                 RayPart &part) {
+    const int wave_log2 = parts_log2 - lane_log2;
+    const int64_t w = t >> 6;
+    const int l = (int)(t & 63);
+    // the wave's slice of 64 >> lane_log2 rays of a tile (or of 64 consecutive rays)
+    const int64_t slice = w >> wave_log2;
+    part.n = 1 << parts_log2;
+    part.j = (int)(w & ((1 << wave_log2) - 1)) << lane_log2 | (l & ((1 << lane_log2) - 1));
+    return ray_of_thread(slice << (6 - lane_log2) | (l >> lane_log2), n, width);
 }
 
 // ------------------------------------------------------------------ ray loads
