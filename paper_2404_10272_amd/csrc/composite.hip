@@ -10,7 +10,7 @@
 // with the suffix sum accumulated in a reverse pass (not as C minus a
 // prefix) and T rebuilt from the exponent sum, whose absolute error stays
 // at the level of one rounding of the ray's total optical depth.  One 16-lane
-// row (a DPP row) handles one ray, 16 consecutive samples per chunk.
+// row (a DPP row) handles one ray, four consecutive samples a lane.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -49,25 +49,132 @@ __device__ __forceinline__ float row_suffix(float x) {
     x += dpp<0x108>(x);
     return x;
 }
-// value of lane `src` (0..15) of this lane's row
-__device__ __forceinline__ float row_lane(float x, int src) {
-    return __shfl(x, ((int)threadIdx.x & 63 & ~(kRow - 1)) | src, 64);
+// value of lane kLane (0..15) of this lane's row
+template <int kLane>
+__device__ __forceinline__ float row_bcast(float x) {
+    return dpp<0x150 + kLane>(x);
 }
 
-// Samples of one row are loaded kGroup chunks of 16 at a time, all loads of a
-// group issued before any of its arithmetic, so that one memory latency
-// covers kGroup * 16 samples instead of 16.  The backward keeps the ray's last
-// group in registers between its two passes, so a larger group there means
-// more rays read their inputs once.
-constexpr int kGroup = 4;
-constexpr int kSpan = kGroup * kRow;
-constexpr int kGroupBwd = 8;
-constexpr int kSpanBwd = kGroupBwd * kRow;
+// Each lane takes kPer consecutive samples of its row's ray, so a row covers
+// kChunk samples per pass and reads them with 16-byte loads (three for t0, t1
+// and sigma, three for the colours), where one sample a lane took six 4-byte
+// loads each.  A group starts wherever the ray does: the loads are aligned to
+// 4 bytes, not 16, which global memory takes at full rate.
+constexpr int kPer = 4;
+constexpr int kChunk = kPer * kRow;
 
-// One 16-lane row per ray, 16 consecutive samples per chunk (coalesced
-// loads); the optical depth before each sample is a row prefix sum plus the
-// carry of the earlier chunks.  Rows past the last ray do nothing, but stay
-// in their wave so that every DPP source lane is active.
+struct __attribute__((packed, aligned(4))) Quad {
+    float v[4];
+};
+__device__ __forceinline__ void load4(const float *p, float v[4]) {
+    const Quad q = *reinterpret_cast<const Quad *>(p);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = q.v[k];
+}
+__device__ __forceinline__ void store4(float *p, float a, float b, float c, float d) {
+    *reinterpret_cast<Quad *>(p) = Quad{{a, b, c, d}};
+}
+
+// Step lengths and optical depths of samples i .. i+3 of a ray ending at b
+// (zero past it), and their colours when rgb is given.  A group may run past
+// the ray into the next one's samples, whose values are dropped; only past
+// `total`, the end of all rays' samples, is nothing read.
+template <bool kColour>
+__device__ __forceinline__ void load_group(int64_t i, int64_t b, int64_t total, const float *__restrict__ t0,
+                                           const float *__restrict__ t1, const float *__restrict__ sigma,
+                                           const float *__restrict__ rgb, float dt[kPer], float tau[kPer],
+                                           float c[3 * kPer]) {
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) dt[k] = tau[k] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 3 * kPer; ++k) c[k] = 0.f;
+    if (i >= b) return;
+    float u[kPer], v[kPer], s[kPer];
+    if (i + kPer <= total) {
+        load4(t0 + i, u);
+        load4(t1 + i, v);
+        load4(sigma + i, s);
+        if (kColour) {
+            load4(rgb + 3 * i, c);
+            load4(rgb + 3 * i + 4, c + 4);
+            load4(rgb + 3 * i + 8, c + 8);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            u[k] = v[k] = s[k] = 0.f;
+            if (i + k < b) {
+                u[k] = t0[i + k];
+                v[k] = t1[i + k];
+                s[k] = sigma[i + k];
+                if (kColour) {
+                    c[3 * k] = rgb[3 * (i + k)];
+                    c[3 * k + 1] = rgb[3 * (i + k) + 1];
+                    c[3 * k + 2] = rgb[3 * (i + k) + 2];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const bool ok = i + k < b;
+        dt[k] = ok ? v[k] - u[k] : 0.f;
+        tau[k] = ok ? s[k] * dt[k] : 0.f;
+        if (kColour) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) c[3 * k + q] = ok ? c[3 * k + q] : 0.f;
+        }
+    }
+}
+
+// exp(-x), by the hardware's base-2 exponential of a product kept to twice
+// the precision of a float (x up to a few hundred otherwise loses bits there)
+__device__ __forceinline__ float exp_neg(float x) {
+    constexpr float L = 1.44269502f, l = 1.92596303e-8f;   // log2(e) = L + l
+    const float y = -x * L;
+    const float e = fmaf(-x, L, -y) - x * l;
+    const float p = __builtin_amdgcn_exp2f(y);
+    return __builtin_isfinite(y) ? fmaf(p, e * 0.693147181f, p) : p;
+}
+
+// alpha = 1 - exp(-tau) of four samples.  Up to half an optical depth it is
+// tau - tau^2 (1/2 - tau/6 + ...), the series truncated below 1.1e-8 of it and
+// rounded once at the end; 1 - exp(-tau) would cancel there.  Thicker samples
+// are rare enough that a wave mostly skips their exponential.
+__device__ __forceinline__ void alphas(const float tau[kPer], float alpha[kPer]) {
+    bool thick = false;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const float x = tau[k];
+        float s = fmaf(x, -1.f / 40320.f, 1.f / 5040.f);
+        s = fmaf(x, -s, 1.f / 720.f);
+        s = fmaf(x, -s, 1.f / 120.f);
+        s = fmaf(x, -s, 1.f / 24.f);
+        s = fmaf(x, -s, 1.f / 6.f);
+        s = fmaf(x, -s, 0.5f);
+        alpha[k] = fmaf(x, -(x * s), x);
+        thick = thick || !(fabsf(x) <= 0.5f);
+    }
+    if (thick) {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (!(fabsf(tau[k]) <= 0.5f)) alpha[k] = 1.f - exp_neg(tau[k]);
+    }
+}
+
+// One 16-lane row per ray.  The optical depth before a lane's samples is a
+// row prefix sum of the lanes' depths plus the carry of earlier chunks; every
+// sample's transmittance is an exponential of its own (multiplying one on
+// along the lane costs less and rounds more).  Rows past the last ray do
+// nothing, but stay in their wave so that every DPP source lane is active.
+//
+// Bound by HBM reads, whose latency the resident waves (5.9 a SIMD on average)
+// and the arithmetic (74 us of VALU issue) do not hide in full: 640,000 rays
+// with 25.4 M samples, 614 MB, take 128 us, 4.8 TB/s; one sample a lane took
+// 158 us, and a bare read of as many bytes takes 85.  Measured no better: two
+// chunks loaded together (139 us), eight lanes a ray (140 us; 20.7 against
+// 27.9 us where rays average 8 samples), a persistent grid that loads the next
+// ray's offsets ahead (138 to 159 us).
 __global__ void __launch_bounds__(kBlock) composite_fwd_kernel(const int64_t *__restrict__ offsets, int64_t n_rays,
                                                               const float *__restrict__ t0,
                                                               const float *__restrict__ t1,
@@ -77,33 +184,24 @@ __global__ void __launch_bounds__(kBlock) composite_fwd_kernel(const int64_t *__
     const int l = threadIdx.x & (kRow - 1);
     const int64_t r = (int64_t)blockIdx.x * kRaysPerBlock + (threadIdx.x / kRow);
     const bool live = r < n_rays;
-    const int64_t a = live ? offsets[r] : 0, b = live ? offsets[r + 1] : 0;
+    const int64_t a = live ? offsets[r] : 0, b = live ? offsets[r + 1] : 0, total = offsets[n_rays];
     float cr = 0.f, cg = 0.f, cb = 0.f, acc = 0.f, carry = 0.f;
-    for (int64_t g0 = a; g0 < b; g0 += kSpan) {   // row-uniform
-        float tau[kGroup], xr[kGroup], xg[kGroup], xb[kGroup];
+    for (int64_t g0 = a; g0 < b; g0 += kChunk) {   // row-uniform
+        float dt[kPer], tau[kPer], c[3 * kPer], alpha[kPer];
+        load_group<true>(g0 + kPer * l, b, total, t0, t1, sigma, rgb, dt, tau, c);
+        alphas(tau, alpha);
+        const float incl = row_prefix((tau[0] + tau[1]) + (tau[2] + tau[3]));
+        float depth = carry + dpp<0x111>(incl);
 #pragma unroll
-        for (int c = 0; c < kGroup; ++c) {
-            const int64_t i = g0 + c * kRow + l;
-            tau[c] = xr[c] = xg[c] = xb[c] = 0.f;
-            if (i < b) {
-                tau[c] = sigma[i] * (t1[i] - t0[i]);
-                xr[c] = rgb[3 * i + 0];
-                xg[c] = rgb[3 * i + 1];
-                xb[c] = rgb[3 * i + 2];
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < kGroup; ++c) {
-            if (g0 + c * kRow >= b) break;   // row-uniform
-            const float incl = row_prefix(tau[c]);
-            const float T = expf(-(carry + incl - tau[c]));
-            const float w = g0 + c * kRow + l < b ? T * (-expm1f(-tau[c])) : 0.f;
-            cr += w * xr[c];
-            cg += w * xg[c];
-            cb += w * xb[c];
+        for (int k = 0; k < kPer; ++k) {
+            const float w = exp_neg(depth) * alpha[k];
+            cr = fmaf(w, c[3 * k], cr);
+            cg = fmaf(w, c[3 * k + 1], cg);
+            cb = fmaf(w, c[3 * k + 2], cb);
             acc += w;
-            carry += row_lane(incl, kRow - 1);
+            depth += tau[k];
         }
+        carry += row_bcast<kRow - 1>(incl);
     }
     cr = row_prefix(cr);
     cg = row_prefix(cg);
@@ -117,11 +215,24 @@ __global__ void __launch_bounds__(kBlock) composite_fwd_kernel(const int64_t *__
     }
 }
 
-// One 16-lane row per ray.  Pass 1: the ray's total optical depth; its last
-// group of chunks stays in registers.  Pass 2, groups and chunks from the
-// back: T_i and T_{i+1} from the total minus the depth at and after i (row
-// suffix sum plus the carry of later chunks), and sum_{k>i} w_k c_k by a row
-// suffix sum plus the carry -- never as C minus a prefix.
+// One 16-lane row per ray, in spans of kKeep chunks.  Pass 1: the optical
+// depth before the ray's last span, which stays in registers.  Pass 2, spans
+// from the back: T_i from the depth before it (the span's, less a span at each
+// step back, plus row prefix sums), and S_i = sum_{k>i} w_k q_k by a row
+// suffix sum plus the carry -- never as C minus a prefix.  The upstream
+// gradient is constant along a ray, so a sample's colour enters only as
+// q_i = g_C . c_i + g_A, the opacity being
+// one more channel of colour one (T_n = T_{i+1} - sum_{k>i} w_k):
+//   dL/dsigma_i = dt_i (T_{i+1} q_i - S_i).
+// One suffix sum instead of three, and one register a sample instead of three;
+// the products of q are summed in 64 bits, as they may cancel.
+//
+// Bound by HBM: 640,000 rays with 25.4 M samples, 614 MB in and 407 MB out,
+// take 263 us, 3.9 TB/s; one sample a lane took 375 us.  kKeep = 1: with two
+// chunks a span 270 us (170 against 164 at 24 samples a ray, 65 against 54 at
+// 8, 287 against 292 at 96), with three 302 and with four 351, as more
+// registers leave fewer waves.
+constexpr int kKeep = 1;
 __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
     const int64_t *__restrict__ offsets, int64_t n_rays, int64_t n_samples, const float *__restrict__ t0,
     const float *__restrict__ t1,
@@ -130,79 +241,97 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
     const int l = threadIdx.x & (kRow - 1);
     const int64_t r = (int64_t)blockIdx.x * kRaysPerBlock + (threadIdx.x / kRow);
     const bool live = r < n_rays;
-    const int64_t a = live ? offsets[r] : 0, b = live ? offsets[r + 1] : 0;
-    const int64_t last = b > a ? a + ((b - a - 1) / kSpanBwd) * kSpanBwd : a;   // first sample of the last group
-    float dt[kGroupBwd], tau[kGroupBwd], xr[kGroupBwd], xg[kGroupBwd], xb[kGroupBwd];
-    auto load_group = [&](int64_t g0) {
-#pragma unroll
-        for (int c = 0; c < kGroupBwd; ++c) {
-            const int64_t i = g0 + c * kRow + l;
-            dt[c] = tau[c] = xr[c] = xg[c] = xb[c] = 0.f;
-            if (i < b) {
-                dt[c] = t1[i] - t0[i];
-                tau[c] = sigma[i] * dt[c];
-                xr[c] = rgb[3 * i + 0];
-                xg[c] = rgb[3 * i + 1];
-                xb[c] = rgb[3 * i + 2];
-            }
-        }
-    };
-
-    float part = 0.f;
-    for (int64_t g0 = a; g0 < last; g0 += kSpanBwd) {   // whole groups before the last
-        float q[kGroupBwd];
-#pragma unroll
-        for (int c = 0; c < kGroupBwd; ++c) {
-            const int64_t i = g0 + c * kRow + l;
-            q[c] = sigma[i] * (t1[i] - t0[i]);
-        }
-#pragma unroll
-        for (int c = 0; c < kGroupBwd; ++c) part += q[c];
-    }
-    load_group(last);
-#pragma unroll
-    for (int c = 0; c < kGroupBwd; ++c) part += tau[c];
-    const float total = row_lane(row_prefix(part), kRow - 1);
-
+    const int64_t a = live ? offsets[r] : 0, b = live ? offsets[r + 1] : 0, hi = offsets[n_rays];
     const float gr = live ? g_rgb[3 * r + 0] : 0.f, gg = live ? g_rgb[3 * r + 1] : 0.f;
     const float gb = live ? g_rgb[3 * r + 2] : 0.f;
-    const float ga = live && g_opacity ? g_opacity[r] : 0.f;
-    const float T_end = expf(-total);
-    float after_tau = 0.f;                      // depth of the later chunks
-    float ar = 0.f, ag = 0.f, ab = 0.f;         // sum of w c over the later chunks
-    for (int64_t g0 = last; g0 >= a; g0 -= kSpanBwd) {   // row-uniform
-        if (g0 != last) load_group(g0);
+    const double dr = gr, dg = gg, db = gb, da = live && g_opacity ? g_opacity[r] : 0.f;
+    constexpr int kSpan = kKeep * kChunk;
+    // first sample of the last span (the ray's spans start at a)
+    const int64_t last = b > a ? a + ((b - a - 1) / kSpan) * kSpan : a;
+
+    float dt[kKeep][kPer], tau[kKeep][kPer], q[kKeep][kPer];
+    const auto load_span = [&](int64_t g0) {
 #pragma unroll
-        for (int c = kGroupBwd - 1; c >= 0; --c) {
-            if (g0 + c * kRow >= b) continue;   // row-uniform
-            const int64_t i = g0 + c * kRow + l;
-            const bool ok = i < b;
-            const float sfx_row = row_suffix(tau[c]);
-            const float sfx = sfx_row + after_tau;   // depth at and after i
-            const float T_here = expf(-(total - sfx));
-            const float T_next = expf(-(total - (sfx - tau[c])));
-            const float w = ok ? T_here * (-expm1f(-tau[c])) : 0.f;
-            const float wr = w * xr[c], wg = w * xg[c], wb = w * xb[c];
-            const float qr = row_suffix(wr), qg = row_suffix(wg), qb = row_suffix(wb);
-            const float sr = qr - wr + ar;   // sum over k > i
-            const float sg = qg - wg + ag;
-            const float sb = qb - wb + ab;
-            if (ok) {
-                const float dC = gr * (T_next * xr[c] - sr) + gg * (T_next * xg[c] - sg) + gb * (T_next * xb[c] - sb);
-                d_sigma[i] = dt[c] * (dC + ga * T_end);
-                d_rgb[3 * i + 0] = w * gr;
-                d_rgb[3 * i + 1] = w * gg;
-                d_rgb[3 * i + 2] = w * gb;
+        for (int h = 0; h < kKeep; ++h) {
+            float c[3 * kPer];
+            load_group<true>(g0 + h * kChunk + kPer * l, b, hi, t0, t1, sigma, rgb, dt[h], tau[h], c);
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) 
+                q[h][k] = (float)fma(db, (double)c[3 * k + 2], fma(dg, (double)c[3 * k + 1], fma(dr, (double)c[3 * k], da)));
+        }
+    };
+    float part = 0.f;
+    for (int64_t g0 = a; g0 < last; g0 += kChunk) {   // the spans before the last
+        float u[kPer], v[kPer], none[3 * kPer];
+        load_group<false>(g0 + kPer * l, b, hi, t0, t1, sigma, rgb, u, v, none);
+        part += (v[0] + v[1]) + (v[2] + v[3]);
+    }
+    load_span(last);
+    float depth = row_bcast<kRow - 1>(row_prefix(part));   // before the span
+    float later = 0.f;                                     // sum of w q over the later chunks
+    for (int64_t g0 = last; g0 >= a; g0 -= kSpan) {   // row-uniform
+        if (g0 != last) load_span(g0);
+        float before[kKeep], all[kKeep];   // depth before the lane in its chunk, of the chunk
+#pragma unroll
+        for (int h = 0; h < kKeep; ++h) {
+            const float incl = row_prefix((tau[h][0] + tau[h][1]) + (tau[h][2] + tau[h][3]));
+            before[h] = dpp<0x111>(incl);
+            all[h] = row_bcast<kRow - 1>(incl);
+        }
+        if (g0 != last) {
+#pragma unroll
+            for (int h = 0; h < kKeep; ++h) depth -= all[h];
+        }
+        if (g0 == a) depth = 0.f;
+        float at[kKeep];
+        at[0] = depth;
+#pragma unroll
+        for (int h = 1; h < kKeep; ++h) at[h] = at[h - 1] + all[h - 1];
+#pragma unroll
+        for (int h = kKeep - 1; h >= 0; --h) {
+            if (g0 + h * kChunk >= b) continue;   // row-uniform
+            const int64_t i = g0 + h * kChunk + kPer * l;
+            float alpha[kPer], w[kPer], next[kPer];   // next: T_{i+1}
+            alphas(tau[h], alpha);
+            float d = at[h] + before[h];
+            float T = exp_neg(d);
+            float wq = 0.f;
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                w[k] = T * alpha[k];
+                d += tau[h][k];
+                next[k] = T = exp_neg(d);
+                wq = fmaf(w[k], q[h][k], wq);
             }
-            after_tau += row_lane(sfx_row, 0);
-            ar += row_lane(qr, 0);
-            ag += row_lane(qg, 0);
-            ab += row_lane(qb, 0);
+            const float qs = row_suffix(wq);
+            float S = dpp<0x101>(qs) + later;   // sum over the samples of later lanes and chunks
+            float ds[kPer];
+#pragma unroll
+            for (int k = kPer - 1; k >= 0; --k) {
+                ds[k] = dt[h][k] * fmaf(next[k], q[h][k], -S);
+                S = fmaf(w[k], q[h][k], S);
+            }
+            if (i + kPer <= b) {
+                store4(d_sigma + i, ds[0], ds[1], ds[2], ds[3]);
+                store4(d_rgb + 3 * i, w[0] * gr, w[0] * gg, w[0] * gb, w[1] * gr);
+                store4(d_rgb + 3 * i + 4, w[1] * gg, w[1] * gb, w[2] * gr, w[2] * gg);
+                store4(d_rgb + 3 * i + 8, w[2] * gb, w[3] * gr, w[3] * gg, w[3] * gb);
+            } else {
+#pragma unroll
+                for (int k = 0; k < kPer; ++k)
+                    if (i + k < b) {
+                        d_sigma[i + k] = ds[k];
+                        d_rgb[3 * (i + k) + 0] = w[k] * gr;
+                        d_rgb[3 * (i + k) + 1] = w[k] * gg;
+                        d_rgb[3 * (i + k) + 2] = w[k] * gb;
+                    }
+            }
+            later += row_bcast<0>(qs);
         }
         if (g0 == a) break;
     }
     // samples no ray owns (before offsets[0], from offsets[n_rays] on) get zero gradient
-    const int64_t lo = offsets[0], hi = offsets[n_rays];
+    const int64_t lo = offsets[0];
     const int64_t before = lo < n_samples ? lo : n_samples, after = hi < n_samples ? n_samples - hi : 0;
     for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < before + after; k += (int64_t)gridDim.x * kBlock) {
         const int64_t i = k < before ? k : hi + (k - before);
@@ -211,6 +340,12 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
         d_rgb[3 * i + 1] = 0.f;
         d_rgb[3 * i + 2] = 0.f;
     }
+}
+
+constexpr int kGroup = 4;
+constexpr int kSpan = kGroup * kRow;
+__device__ __forceinline__ float row_lane(float x, int src) {
+    return __shfl(x, ((int)threadIdx.x & 63 & ~(kRow - 1)) | src, 64);
 }
 
 // ------------------------------------------------------------------ blob field
