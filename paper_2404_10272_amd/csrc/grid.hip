@@ -4,15 +4,16 @@
 // dense uint8 occupancy, plus decoding back to dense for round-trip checks.
 //
 // VDB build, all on the device:
-//   1. classify: one wave per 8^3 block slot packs the block into its
-//      512-bit mask (lane = (x, y) row of 8 z-voxels) and marks it empty,
-//      full or mixed;
+//   1. classify: one workgroup per column of 8^3 blocks packs each block into
+//      its 512-bit mask and marks it empty, full or mixed;
 //   2. root: per root cell, all slots empty -> empty root tile, all full ->
 //      full root tile, else an internal node;
 //   3. exclusive scans number the nodes and the leaves (mixed blocks under
 //      node roots, in root-then-slot order);
 //   4. write the root table, node masks (child, value, per-word leaf rank),
 //      the nodes' per-slot child tables and leaf masks.
+// One workgroup does 2, 3 and the nodes' part of 4 for trees of up to 1,024
+// mask words (65,536 block slots in nodes of 64 and more).
 #pragma clang fp contract(off)
 
 #include <hip/hip_runtime.h>
@@ -205,23 +206,17 @@ struct BuildDims {
     int W;            // words per node mask
 };
 
-// block slot e -> voxel base of its 8^3 block
-__device__ __forceinline__ void block_base(const BuildDims &b, int64_t e, int &lev, int &x0, int &y0, int &z0) {
-    int64_t root = e / b.n_slot;
-    int slot = (int)(e % b.n_slot);
-    lev = (int)(root / ((int64_t)b.NR * b.NR * b.NR));
-    int rl = (int)(root % ((int64_t)b.NR * b.NR * b.NR));
-    int rx = rl / (b.NR * b.NR), ry = (rl / b.NR) % b.NR, rz = rl % b.NR;
-    int sx = slot / (b.S * b.S), sy = (slot / b.S) % b.S, sz = slot % b.S;
-    x0 = rx * b.D + sx * 8;
-    y0 = ry * b.D + sy * 8;
-    z0 = rz * b.D + sz * 8;
+// Slot of the 8^3 block (xb, yb, zb) of a level (block coordinates over the
+// padded grid, NR*S a side).
+__device__ __forceinline__ int64_t block_slot(const BuildDims &b, int lev, int xb, int yb, int zb) {
+    const int lg = b.ilog2, m = b.S - 1;
+    const int64_t root = (((int64_t)lev * b.NR + (xb >> lg)) * b.NR + (yb >> lg)) * b.NR + (zb >> lg);
+    return root * b.n_slot + (((((xb & m) << lg) | (yb & m)) << lg) | (zb & m));
 }
 
-// Occupancy as bytes of 8 voxels along z, row by row: byte (row, zb) holds
-// voxels z = 8zb .. 8zb+7 of row ((l*R + x)*R + y), bit z & 7, for
-// Rb = ceil(R/8) bytes per row.  One thread per byte, so consecutive threads
-// read consecutive 8-voxel runs (16- or 32-byte loads when the rows allow).
+// Occupancy as bytes of 8 voxels along z: byte() of the run of cnt <= 8 voxels
+// from `base` on, bit z & 7.  Consecutive threads read consecutive runs (16- or
+// 32-byte loads when the rows allow).
 struct OccSource {        // uint8 occupancy, nonzero = occupied
     const uint8_t *occ;
     __device__ __forceinline__ uint8_t byte(uint64_t base, int cnt, bool vec) const {
@@ -288,64 +283,235 @@ struct DensitySource {    // density cache, updated and thresholded (DensityUpda
     }
 };
 
+// One workgroup per column of 8x8 voxel rows of a level: the rows' bits go to
+// LDS as bytes of 8 voxels, then eight threads a block make its eight leaf words
+// (word x, bit y*8 + z) and its kind (0 empty, 1 full, 2 mixed).  With
+// `partial` (a refresh), the words are compared with the previous ones (masks):
+// the block is marked dirty when they differ, and partial[workgroup] is set to
+// the voxels that flipped and whether some block's kind changed, which is what
+// forces the tree to be renumbered.
+//
+// Bound by HBM where the source is a density cache (12 bytes a voxel): the
+// column's 64 rows are read in whole, and nothing between the voxels and the
+// leaf words goes through memory: 20 us for four 128^3 levels, 101 MB, 5 TB/s.
+// The changes are summed in a workgroup, not by an atomic a block: those took
+// 68 us on the same refresh.
+constexpr int kMaxBlocksPerAxis = OGV_MAX_RES / 8;
 template <class Src>
-__global__ void __launch_bounds__(256) row_bits_kernel(Src src, int L, int R, bool vec, uint8_t *__restrict__ rows) {
-    const int Rb = (R + 7) >> 3;
-    const uint64_t n = (uint64_t)L * R * R * Rb;
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const uint64_t row = t / Rb;
-    const int z0 = (int)(t % Rb) * 8;
-    rows[t] = src.byte(row * R + z0, min(8, R - z0), vec);
+__global__ void __launch_bounds__(256) column_classify_kernel(BuildDims b, Src src, bool vec,
+                                                             int32_t *__restrict__ kind, int32_t *__restrict__ mixed,
+                                                             uint64_t *__restrict__ masks, int32_t *__restrict__ dirty,
+                                                             int2 *__restrict__ partial) {
+    __shared__ __align__(16) uint8_t rows[kMaxBlocksPerAxis][64];   // [zb][x*8 + y]
+    __shared__ int32_t sums[2];
+    const int nb = b.NR * b.S, Rb = (b.R + 7) >> 3;
+    const int lev = blockIdx.x / (nb * nb), xb = blockIdx.x / nb % nb, yb = blockIdx.x % nb;
+    if (threadIdx.x < 2) sums[threadIdx.x] = 0;
+    for (int t = threadIdx.x; t < 64 * nb; t += 256) {
+        const int row = t / nb, zb = t - row * nb;
+        const int x = 8 * xb + (row >> 3), y = 8 * yb + (row & 7);
+        uint8_t byte = 0;
+        if (x < b.R && y < b.R && zb < Rb)
+            byte = src.byte((((uint64_t)lev * b.R + x) * b.R + y) * b.R + 8 * zb, min(8, b.R - 8 * zb), vec);
+        rows[zb][row] = byte;
+    }
+    __syncthreads();
+    int32_t flipped = 0, kind_changed = 0;
+    const int x = threadIdx.x & 7, shift = threadIdx.x & 56;
+    for (int z0 = 0; z0 < nb; z0 += 32) {
+        const int zb = z0 + (threadIdx.x >> 3);
+        if (zb >= nb) continue;   // the eight threads of a block together
+        const int64_t e = block_slot(b, lev, xb, yb, zb);
+        const uint64_t word = *reinterpret_cast<const uint64_t *>(&rows[zb][8 * x]);
+        const int32_t diff = partial ? __popcll(word ^ masks[e * 8 + x]) : 0;
+        masks[e * 8 + x] = word;
+        const uint32_t some = (uint32_t)(__ballot(word != 0) >> shift) & 0xff;
+        const uint32_t full = (uint32_t)(__ballot(word == ~0ull) >> shift) & 0xff;
+        const uint32_t dirt = (uint32_t)(__ballot(diff != 0) >> shift) & 0xff;
+        const int k = full == 0xff ? 1 : (some != 0 ? 2 : 0);
+        flipped += diff;
+        if (x == 0) {
+            if (partial) {
+                kind_changed |= k != kind[e];
+                dirty[e] = dirt != 0;
+            }
+            kind[e] = k;
+            mixed[e] = k == 2;
+        }
+    }
+    if (!partial) return;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        flipped += __shfl_xor(flipped, off, 64);
+        kind_changed |= __shfl_xor(kind_changed, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&sums[0], flipped);
+        atomicOr(&sums[1], kind_changed);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) partial[blockIdx.x] = make_int2(sums[0], sums[1]);
 }
 
-// One wave per 8^3 block slot (4 per workgroup): the block's leaf words from
-// the row bytes (word x, bit y*8 + z), its kind (0 empty, 1 full, 2 mixed).
-// With changed (a refresh), the words are compared with the previous ones
-// (masks): the block is marked dirty when they differ, changed[0] gains the
-// voxels that flipped, and changed[1] is set when the block's kind changed,
-// which is what forces the tree to be renumbered.
-__global__ void __launch_bounds__(256) block_classify_kernel(BuildDims b, const uint8_t *__restrict__ rowbits,
-                                                            int32_t *__restrict__ kind, int32_t *__restrict__ mixed,
-                                                            uint64_t *__restrict__ masks, int32_t *__restrict__ dirty,
-                                                            int32_t *__restrict__ changed) {
-    __shared__ uint8_t rows[4][64];
-    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int64_t e = (int64_t)blockIdx.x * 4 + wid;
-    bool live = e < b.n_block;
-    uint8_t byte = 0;
-    if (live) {
-        int lev, x0, y0, z0;
-        block_base(b, e, lev, x0, y0, z0);
-        const int x = x0 + (lane >> 3), y = y0 + (lane & 7);
-        const int Rb = (b.R + 7) >> 3;
-        if (x < b.R && y < b.R && z0 < b.R) byte = rowbits[(((uint64_t)lev * b.R + x) * b.R + y) * Rb + (z0 >> 3)];
-    }
-    rows[wid][lane] = byte;
+// changed[0] = the voxels that flipped, changed[1] = whether a block's kind
+// changed, from the workgroups' partial results.  One workgroup; every thread
+// must call it, and gets changed[1].
+__device__ __forceinline__ int32_t sum_changed(const int2 *__restrict__ partial, int n, int32_t *changed) {
+    __shared__ int32_t sums[2];
+    if (threadIdx.x < 2) sums[threadIdx.x] = 0;
     __syncthreads();
-    if (!live) return;
-    // word x of the leaf = bytes (x, y=0..7): bit y*8 + z
-    uint64_t word = 0;
-    int32_t diff = 0;
-    if (lane < 8) {
-        for (int y = 0; y < 8; ++y) word |= (uint64_t)rows[wid][lane * 8 + y] << (8 * y);
-        if (changed) diff = __popcll(word ^ masks[e * 8 + lane]);
-        masks[e * 8 + lane] = word;
+    int32_t flipped = 0, kind_changed = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const int2 p = partial[i];
+        flipped += p.x;
+        kind_changed |= p.y;
     }
-    const bool any_on = __ballot(lane < 8 && word != 0) != 0;
-    const bool all_on = __ballot(lane < 8 && word == ~0ull) == 0xffull;
-    const int k = all_on ? 1 : (any_on ? 2 : 0);
-    if (changed) {
-        const bool dirt = __ballot(diff != 0) != 0;
-        add_changed(diff, changed);
-        if (lane == 0) {
-            if (k != kind[e]) changed[1] = 1;
-            dirty[e] = dirt;
+    if (flipped) atomicAdd(&sums[0], flipped);
+    if (kind_changed) atomicOr(&sums[1], 1);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        changed[0] = sums[0];
+        changed[1] = sums[1];
+    }
+    return sums[1];
+}
+
+__global__ void __launch_bounds__(256) changed_kernel(const int2 *__restrict__ partial, int n, int32_t *changed) {
+    sum_changed(partial, n, changed);
+}
+
+// The whole numbering of a tree of at most kNumberWords mask words (64 slots of
+// one node each) by one workgroup: root kinds, node and leaf indices, the root
+// table, the node masks and child tables, and the counts.  One launch instead of
+// seven, each of which costs more to start than to run at these sizes: a whole
+// refresh of four 128^3 levels (256 words) takes 46 us from densities and 27
+// from bytes, where the separate kernels took 131 and 54, two 160^3 levels
+// (1,024 words) 91 and 76 against 134 and 90.  At 1,728 words the one workgroup
+// was slower (95 against 84 us from bytes), so longer trees take the separate
+// kernels.  With `partial` it first sums the classification's changes, and
+// numbers nothing when no block changed kind.
+constexpr int kNumberThreads = 1024;
+constexpr int kNumberWords = 1024;
+__global__ void __launch_bounds__(kNumberThreads) number_tree_kernel(
+    BuildDims b, const int32_t *__restrict__ kind, const int2 *__restrict__ partial, int n_partial, int32_t *changed,
+    int64_t *__restrict__ leaf_idx, int32_t *__restrict__ root, uint64_t *__restrict__ child,
+    uint64_t *__restrict__ value, uint32_t *__restrict__ rank, int32_t *__restrict__ slot, VdbCounts *counts) {
+    __shared__ int32_t word_mixed[kNumberWords];   // mixed slots of each word, then its first leaf
+    __shared__ int32_t root_code[kNumberWords];    // full slots << 1 | some mixed; then the root table's entry
+    __shared__ int32_t wave_sum[2][kNumberThreads / 64];
+    __shared__ int32_t tiles[2], roots[2];
+    if (partial) {
+        if (sum_changed(partial, n_partial, changed) == 0) return;
+    }
+    const int n_words = (int)(b.n_root * b.W), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int kWaves = kNumberThreads / 64, kEach = kNumberWords / kNumberThreads;
+    for (int i = threadIdx.x; i < kNumberWords; i += kNumberThreads) word_mixed[i] = root_code[i] = 0;
+    if (threadIdx.x < 2) tiles[threadIdx.x] = roots[threadIdx.x] = 0;
+    __syncthreads();
+    const auto kind_of = [&](int j) {   // of slot `lane` of word j, -1 past the node's slots
+        const int r = j / b.W, s = (j - r * b.W) * 64 + lane;
+        return j < n_words && s < b.n_slot ? kind[(int64_t)r * b.n_slot + s] : -1;
+    };
+    constexpr int kBatch = 8;   // words whose kinds a wave loads together: one round trip for all
+    for (int j0 = wave; j0 < n_words; j0 += kWaves * kBatch) {
+        int k[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) k[q] = kind_of(j0 + q * kWaves);
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+            const int j = j0 + q * kWaves;
+            const int n_mixed = __popcll(__ballot(k[q] == 2)), n_full = __popcll(__ballot(k[q] == 1));
+            if (lane == 0 && j < n_words) {
+                word_mixed[j] = n_mixed;
+                if (n_full) atomicAdd(&root_code[j / b.W], n_full << 1);
+                if (n_mixed) atomicOr(&root_code[j / b.W], 1);
+            }
+        }
+    }
+    __syncthreads();
+    // exclusive scans over the words (leaves) and the roots (nodes), kEach consecutive entries a thread
+    int32_t leaves[kEach], nodes[kEach], leaf_sum = 0, node_sum = 0;
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+        const int i = threadIdx.x * kEach + q;
+        leaves[q] = leaf_sum;
+        nodes[q] = node_sum;
+        leaf_sum += word_mixed[i];
+        // a root cell is a tile when its slots are all empty or all full
+        if (i < b.n_root) node_sum += root_code[i] != 0 && root_code[i] != (int32_t)(b.n_slot << 1);
+    }
+    int32_t leaf_incl = leaf_sum, node_incl = node_sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t x = __shfl_up(leaf_incl, off, 64), y = __shfl_up(node_incl, off, 64);
+        if (lane >= off) {
+            leaf_incl += x;
+            node_incl += y;
+        }
+    }
+    if (lane == 63) {
+        wave_sum[0][wave] = leaf_incl;
+        wave_sum[1][wave] = node_incl;
+    }
+    __syncthreads();
+    int32_t leaf_base = leaf_incl - leaf_sum, node_base = node_incl - node_sum, n_leaves = 0, n_nodes = 0;
+    for (int q = 0; q < kWaves; ++q) {
+        if (q < wave) {
+            leaf_base += wave_sum[0][q];
+            node_base += wave_sum[1][q];
+        }
+        n_leaves += wave_sum[0][q];
+        n_nodes += wave_sum[1][q];
+    }
+    int32_t empty_roots = 0, full_roots = 0;
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+        const int i = threadIdx.x * kEach + q;
+        word_mixed[i] = leaf_base + leaves[q];
+        if (i < b.n_root) {
+            const bool empty = root_code[i] == 0, full = root_code[i] == (int32_t)(b.n_slot << 1);
+            const int32_t entry = empty ? -1 : (full ? -2 : node_base + nodes[q]);
+            empty_roots += empty;
+            full_roots += full;
+            root_code[i] = entry;
+            root[i] = entry;
+        }
+    }
+    if (empty_roots) atomicAdd(&roots[0], empty_roots);
+    if (full_roots) atomicAdd(&roots[1], full_roots);
+    __syncthreads();
+    int32_t n_empty = 0, n_full = 0;   // tiles of the words this wave writes
+    for (int j0 = wave; j0 < n_words; j0 += kWaves * kBatch) {
+        int kinds[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) kinds[q] = kind_of(j0 + q * kWaves);
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {
+            const int j = j0 + q * kWaves, k = kinds[q];
+            if (j >= n_words) break;
+            const int r = j / b.W, w = j - r * b.W, node = root_code[r], s = w * 64 + lane;
+            if (node < 0) continue;
+            const uint64_t cm = __ballot(k == 2), vm = __ballot(k == 1), em = __ballot(k == 0);
+            const int32_t leaf = word_mixed[j] + __popcll(cm & ((1ull << lane) - 1));
+            if (k >= 0) slot[(int64_t)node * b.n_slot + s] = k == 2 ? leaf : (k == 1 ? -2 : -1);
+            if (k == 2) leaf_idx[(int64_t)r * b.n_slot + s] = leaf;
+            if (lane == 0) {
+                child[(int64_t)node * b.W + w] = cm;
+                value[(int64_t)node * b.W + w] = vm;
+                rank[(int64_t)node * b.W + w] = (uint32_t)word_mixed[j];
+            }
+            n_empty += __popcll(em);
+            n_full += __popcll(vm);
         }
     }
     if (lane == 0) {
-        kind[e] = k;
-        mixed[e] = k == 2;
+        atomicAdd(&tiles[0], n_empty);
+        atomicAdd(&tiles[1], n_full);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        leaf_idx[b.n_block] = n_leaves;
+        *counts = VdbCounts{n_nodes, n_leaves, tiles[1], tiles[0], roots[1], roots[0]};
     }
 }
 
@@ -529,34 +695,50 @@ struct VdbBuildState {
     int32_t *kind, *mixed, *root_kind, *is_node;
     uint64_t *masks;
     int64_t *leaf_idx, *node_idx, *tiles;
-    uint8_t *rowbits;   // occupancy as row bytes (row_bits_kernel), L*R*R*ceil(R/8)
     int32_t *dirty;     // per block: its bits changed in the last density refresh
     int32_t *changed;   // [2] of the last density refresh when the caller passes none
+    int2 *partial;      // per classification workgroup: its voxels that flipped, whether a kind changed
 };
 
-// Classifies every 8^3 block of occ and writes the tree into the grid's
-// storage (sized for the worst case at build time): the kernels of a build,
-// all asynchronous on s.
+unsigned columns(const BuildDims &b) { return (unsigned)((int64_t)b.L * b.NR * b.S * b.NR * b.S); }
+bool numbered_at_once(const BuildDims &b) { return b.n_root * b.W <= kNumberWords; }
+
 // The tree from the block kinds and masks left by a classification: root
-// kinds, node and leaf numbering, and the node and leaf records.  gate
-// (nullable) as on the kernels: when it reads 0 only dirty leaves are
-// rewritten.
-hipError_t enqueue_tree(ogv_grid *g, const VdbBuildState &st, const int32_t *gate, hipStream_t s) {
+// kinds, node and leaf numbering, and the node and leaf records, all
+// asynchronous on s.  changed (nullable): the classification compared; its
+// partial changes are summed there, and when no block changed kind only dirty
+// leaves are rewritten.
+hipError_t enqueue_tree(ogv_grid *g, const VdbBuildState &st, int32_t *changed, hipStream_t s) {
     const BuildDims &b = st.b;
     GridView &v = g->view;
-    root_kernel<<<(unsigned)b.n_root, 256, 0, s>>>(b, st.kind, st.root_kind, st.is_node, gate);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = launch_excl_scan(st.is_node, b.n_root, st.node_idx, st.tiles, 0, nullptr, s, gate);
-    if (e == hipSuccess) {
-        root_write_kernel<<<(unsigned)((b.n_root + 255) / 256), 256, 0, s>>>(b, st.root_kind, st.node_idx,
-                                                                            (int32_t *)v.root, g->counts_dev, gate);
+    const int32_t *gate = changed ? changed + 1 : nullptr;
+    const int2 *partial = changed ? st.partial : nullptr;
+    hipError_t e = hipSuccess;
+    if (numbered_at_once(b)) {
+        number_tree_kernel<<<1, kNumberThreads, 0, s>>>(b, st.kind, partial, (int)columns(b), changed, st.leaf_idx,
+                                                        (int32_t *)v.root, (uint64_t *)v.child, (uint64_t *)v.value,
+                                                        (uint32_t *)v.rank, (int32_t *)v.slot, g->counts_dev);
         e = hipGetLastError();
+    } else {
+        if (partial) changed_kernel<<<1, 256, 0, s>>>(partial, (int)columns(b), changed);
+        zero_counts_kernel<<<1, 64, 0, s>>>(g->counts_dev, gate);
+        root_kernel<<<(unsigned)b.n_root, 256, 0, s>>>(b, st.kind, st.root_kind, st.is_node, gate);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = launch_excl_scan(st.is_node, b.n_root, st.node_idx, st.tiles, 0, nullptr, s, gate);
+        if (e == hipSuccess) {
+            root_write_kernel<<<(unsigned)((b.n_root + 255) / 256), 256, 0, s>>>(
+                b, st.root_kind, st.node_idx, (int32_t *)v.root, g->counts_dev, gate);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) e = launch_excl_scan(st.mixed, b.n_block, st.leaf_idx, st.tiles, 0, nullptr, s, gate);
+        if (e == hipSuccess) {
+            node_write_kernel<<<(unsigned)((b.n_root * b.W + 3) / 4), 256, 0, s>>>(
+                b, st.root_kind, st.node_idx, st.kind, st.leaf_idx, (uint64_t *)v.child, (uint64_t *)v.value,
+                (uint32_t *)v.rank, (int32_t *)v.slot, g->counts_dev, gate);
+            e = hipGetLastError();
+        }
     }
-    if (e == hipSuccess) e = launch_excl_scan(st.mixed, b.n_block, st.leaf_idx, st.tiles, 0, nullptr, s, gate);
     if (e == hipSuccess) {
-        node_write_kernel<<<(unsigned)((b.n_root * b.W + 3) / 4), 256, 0, s>>>(
-            b, st.root_kind, st.node_idx, st.kind, st.leaf_idx, (uint64_t *)v.child, (uint64_t *)v.value,
-            (uint32_t *)v.rank, (int32_t *)v.slot, g->counts_dev, gate);
         leaf_write_kernel<<<(unsigned)((b.n_block * 8 + 255) / 256), 256, 0, s>>>(
             b, st.mixed, st.leaf_idx, st.masks, (uint64_t *)v.leaves, (uint64_t *)v.sub, g->counts_dev, gate,
             st.dirty);
@@ -565,36 +747,29 @@ hipError_t enqueue_tree(ogv_grid *g, const VdbBuildState &st, const int32_t *gat
     return e;
 }
 
-unsigned row_bits_blocks(const BuildDims &b) {
-    return (unsigned)(((uint64_t)b.L * b.R * b.R * ((b.R + 7) / 8) + 255) / 256);
-}
-
+// Classifies every 8^3 block of occ and writes the tree into the grid's
+// storage (sized for the worst case at build time): the kernels of a build.
 hipError_t enqueue_vdb(ogv_grid *g, const VdbBuildState &st, const uint8_t *occ, hipStream_t s) {
     const BuildDims &b = st.b;
-    zero_counts_kernel<<<1, 64, 0, s>>>(g->counts_dev, nullptr);
     const bool vec = b.R % 8 == 0 && (uintptr_t)occ % 8 == 0;   // 8-byte loads stay aligned
-    row_bits_kernel<<<row_bits_blocks(b), 256, 0, s>>>(OccSource{occ}, b.L, b.R, vec, st.rowbits);
-    block_classify_kernel<<<(unsigned)((b.n_block + 3) / 4), 256, 0, s>>>(b, st.rowbits, st.kind, st.mixed, st.masks,
-                                                                         st.dirty, nullptr);
+    column_classify_kernel<<<columns(b), 256, 0, s>>>(b, OccSource{occ}, vec, st.kind, st.mixed, st.masks, st.dirty,
+                                                      (int2 *)nullptr);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = enqueue_tree(g, st, nullptr, s);
     return e;
 }
 
-// Refresh from the density cache: classification with the threshold fused in,
-// then the tree rebuilt -- renumbered when a block's kind changed, else only
-// the leaves whose bits changed rewritten (every launch reads changed[1]).
+// Refresh from the density cache: classification with the update and threshold
+// fused in, then the tree rebuilt -- renumbered when a block's kind changed,
+// else only the leaves whose bits changed rewritten.
 hipError_t enqueue_vdb_density(ogv_grid *g, const VdbBuildState &st, const DensityUpdate &u, int32_t *changed,
                                hipStream_t s) {
     const BuildDims &b = st.b;
-    zero_changed_kernel<<<1, 64, 0, s>>>(changed);
     const bool vec = b.R % 4 == 0 && ((uintptr_t)u.cache | (uintptr_t)u.density) % 16 == 0;   // 16-byte accesses aligned
-    row_bits_kernel<<<row_bits_blocks(b), 256, 0, s>>>(DensitySource{u}, b.L, b.R, vec, st.rowbits);
-    block_classify_kernel<<<(unsigned)((b.n_block + 3) / 4), 256, 0, s>>>(b, st.rowbits, st.kind, st.mixed, st.masks,
-                                                                         st.dirty, changed);
-    zero_counts_kernel<<<1, 64, 0, s>>>(g->counts_dev, changed + 1);
+    column_classify_kernel<<<columns(b), 256, 0, s>>>(b, DensitySource{u}, vec, st.kind, st.mixed, st.masks, st.dirty,
+                                                      st.partial);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = enqueue_tree(g, st, changed + 1, s);
+    if (e == hipSuccess) e = enqueue_tree(g, st, changed, s);
     return e;
 }
 
@@ -765,8 +940,8 @@ extern "C" ogv_status ogv_vdb_build(int32_t L, int32_t R, const float *boxes, co
     size_t t_nodeidx = take(sizeof(int64_t) * (b.n_root + 1));
     size_t t_tiles = take(sizeof(int64_t) * (scan_tiles(b.n_block) + 1));
     size_t t_dirty = take(sizeof(int32_t) * b.n_block);
-    size_t t_rowbits = take((size_t)L * R * R * ((R + 7) / 8));
     size_t t_changed = take(sizeof(int32_t) * 2);
+    size_t t_partial = take(sizeof(int2) * (size_t)columns(b));
     size_t scratch_total = off;
 
     ogv_grid *g = new ogv_grid();
@@ -817,8 +992,8 @@ extern "C" ogv_status ogv_vdb_build(int32_t L, int32_t R, const float *boxes, co
     bs->is_node = (int32_t *)(t + t_isnode);
     bs->tiles = (int64_t *)(t + t_tiles);
     bs->dirty = (int32_t *)(t + t_dirty);
-    bs->rowbits = (uint8_t *)(t + t_rowbits);
     bs->changed = (int32_t *)(t + t_changed);
+    bs->partial = (int2 *)(t + t_partial);
 
     hipError_t e = hipMemcpyAsync((void *)v.boxes, g->boxes_host, sizeof(float) * 6 * L, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
