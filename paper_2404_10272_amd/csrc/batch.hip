@@ -28,7 +28,6 @@ namespace ogv {
 namespace {
 
 constexpr int kMaxScenes = 64;
-static_assert(kMaxScenes <= kBlock, "the expansion stages every scene's lattice, one per thread");
 
 struct SceneDesc {
     GridView g;
@@ -179,7 +178,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kEx
                                                               const int32_t *__restrict__ n_lost) {
     // the offsets are read only (no scan inside the expansion)
     expand_block(const_cast<int64_t *>(offsets), ChunkScan{}, n_total, nruns, rd, SceneLattices{lats, first, n_scenes},
-                 capacity, ray_ids, t0, t1, vec4 != 0);
+                 capacity, ray_ids, t0, t1, vec4 != 0, nullptr);
     batch_fill_lost<kSkip>(scenes, n_scenes, lost, n_lost, offsets, capacity, ray_ids, t0, t1);
 }
 

@@ -92,7 +92,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kEx
                                                         float *__restrict__ t0, float *__restrict__ t1, int vec4,
                                                         const int32_t *__restrict__ lost,
                                                         const int32_t *__restrict__ n_lost) {
-    expand_block<kScan>(offsets, cs, n_rays, nruns, rd, OneLattice{lat}, capacity, ray_ids, t0, t1, vec4 != 0);
+    extern __shared__ __align__(16) uint32_t smem[];   // the lattice's points, when they fit (kTableLds)
+    expand_block<kScan>(offsets, cs, n_rays, nruns, rd, OneLattice{lat}, capacity, ray_ids, t0, t1, vec4 != 0,
+                        (float *)smem);
     const int64_t m = *n_lost;
     if (m == 0) return;
     const Tree tree = reads_tree(kGrid) ? load_tree<false>(g, nullptr) : Tree{};
@@ -518,6 +520,7 @@ ogv_status expand(const ogv_grid *grid, int32_t variant, const float *o, const f
                   bool write, int64_t cap, int32_t *ids, float *t0, float *t1, int32_t *overflow, const Lattice &lat,
                   const Bufs &b, hipStream_t s) {
     const unsigned blocks = (unsigned)min(expand_items(b.rows), (int64_t)INT32_MAX);
+    const size_t shm = lat.cone && lat.n_tab <= kTableLds ? sizeof(float) * (size_t)lat.n_tab : 0;
     const int vec4 = (((uintptr_t)ids | (uintptr_t)t0 | (uintptr_t)t1) & 15) == 0;
     const GridView &g = grid->view;
     const ChunkScan cs = scan ? ChunkScan{b.counts, b.tiles, b.csums, overflow, b.parts_log2, write ? 1 : 0} : ChunkScan{};
@@ -526,11 +529,11 @@ ogv_status expand(const ogv_grid *grid, int32_t variant, const float *o, const f
 #define OGV_LAUNCH(V, K, L)                                                                                          \
     do {                                                                                                             \
         if (scan)                                                                                                    \
-            expand_kernel<V, K, true><<<blocks, kBlock, 0, s>>>(g, o, d, offsets, cs, b.rows, b.nruns, reader_of(b), \
+            expand_kernel<V, K, true><<<blocks, kBlock, shm, s>>>(g, o, d, offsets, cs, b.rows, b.nruns, reader_of(b), \
                                                                 lat, cap, ids, t0, t1, vec4, b.pool.lost,            \
                                                                 b.pool.n_lost);                                      \
         else                                                                                                         \
-            expand_kernel<V, K, false><<<blocks, kBlock, 0, s>>>(g, o, d, offsets, cs, b.rows, b.nruns,              \
+            expand_kernel<V, K, false><<<blocks, kBlock, shm, s>>>(g, o, d, offsets, cs, b.rows, b.nruns,              \
                                                                  reader_of(b), lat, cap, ids, t0, t1, vec4,          \
                                                                  b.pool.lost, b.pool.n_lost);                        \
     } while (0)

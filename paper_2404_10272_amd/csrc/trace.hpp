@@ -1011,19 +1011,32 @@ __device__ __forceinline__ void trace_ray(const GridView &g, const Tree &tree, c
 // group) are dealt round-robin to kExpandParts blocks, so a chunk dense with
 // samples does not run its windows one after another in one block while the
 // rest of the chip has finished.
-// Block-relative offsets fit in 32 bits: a ray has at most 2^24 lattice
-// points, so 256 rays stay below 2^32 outputs.
+// Outputs counted from the chunk's first group fit in 32 bits: a ray has fewer
+// than 2^24 samples, so 256 rays and the three outputs before them stay below
+// 2^32.
+// A group looks at most four runs back and reads each output's run whole (first
+// index and ray, 8 bytes); a growing step's points come from LDS when they
+// fit, so that the write loop issues no global load: one counter covers
+// loads and stores on this architecture, and a load waits for every store
+// before it.  A 1280 x 832 frame on four cascades with 244 million samples
+// went from 709 to 561 us (5.2 TB/s of output), with the points in LDS.  Scans
+// by the vector unit's lane moves and run slots loaded four at a time took 1 to
+// 1.5 us off every block: a 64 x 64 frame's expansion 9.4 to 8.0 us.
+// Tried beside it: the same work by single waves, 64 rows each, without any
+// barrier (20 to 50% slower on frames, whose rows with many samples then sit
+// in few waves, 5% slower with the samples dealt out evenly).
 constexpr int kExpandRuns = 1024;     // runs staged per pass
 constexpr int kExpandGroups = 2048;   // 4-output groups per owner window
 constexpr int kExpandParts = 4;       // blocks sharing one chunk's windows
 // Waves per SIMD asked of the expansion kernels: six blocks of 256 lanes per CU
-// (LDS allows six).  At the register budget this leaves (80 VGPRs) the
+// (LDS allows seven, without a table).  At the register budget this leaves (80 VGPRs) the
 // expansion keeps its loops free of spills; only the rarely taken lost-ray
 // traversal spills (the -O1 build; at -O2 the growing-step path spilled as
 // well).  An expansion block
 // spends much of its life waiting on loads and barriers while the other
 // blocks' stores fill HBM, so residency is what keeps the writes flowing.
 constexpr int kExpandWaves = 6;
+constexpr int kTableLds = 4096;       // growing-step lattice points kept in LDS, at most
 constexpr int kGroupsPerLane = kExpandGroups / kBlock;
 constexpr int kOwnerBits = 11;        // owner entries: window number << 11 | (1 + run), run < 1024
 // The owner map is padded with one word after every kGroupsPerLane entries:
@@ -1037,21 +1050,22 @@ __device__ __forceinline__ int own_slot(int g) { return g + g / kGroupsPerLane; 
 struct OneLattice {       // every ray on one lattice
     static constexpr bool kMulti = false;
     Lattice lat;
-    __device__ __forceinline__ int scene_of(int64_t) const { return 0; }
-    __device__ __forceinline__ Lattice get(int) const { return lat; }
 };
 
 struct SceneLattices {    // ray r on the lattice of its scene
     static constexpr bool kMulti = true;
-    const Lattice *lats;   // [n], n <= kBlock
+    const Lattice *lats;   // [n]
     const int64_t *first;  // first global ray of each scene, [n + 1]
     int n;
+    // of a wave-uniform ray
     __device__ __forceinline__ int scene_of(int64_t r) const {
         int s = 0;
-        while (s + 1 < n && first[s + 1] <= r) ++s;
+        for (int b = 1; b < n; b += 64) {
+            const int k = b + (int)(threadIdx.x & 63);
+            s += __popcll(__ballot(k < n && first[min(k, n)] <= r));
+        }
         return s;
     }
-    __device__ __forceinline__ Lattice get(int s) const { return lats[s]; }
 };
 
 struct RunReader {
@@ -1062,25 +1076,41 @@ struct RunReader {
     const int32_t *chunk_next;
 };
 
-__device__ __forceinline__ int64_t block_incl_scan256(int64_t x, int64_t *lds, int64_t &total) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        int64_t y = __shfl_up(x, off, 64);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) lds[wid] = x;
-    __syncthreads();
-    int64_t base = 0;
-    total = 0;
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
-        int64_t v = lds[w];
-        if (w < wid) base += v;
-        total += v;
-    }
-    __syncthreads();
-    return base + x;   // inclusive
+// Inclusive scans over the 64 lanes: row shifts by 1, 2, 4, 8, then lane 15 of a
+// row of 16 to the next of rows 1 and 3, and lane 31 to rows 2 and 3 (lanes that
+// nothing is moved to add 0).  Through the vector unit's own lane moves these
+// take a tenth of the time of six exchanges through LDS.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ int32_t lanes_moved(int32_t v) {
+    return __builtin_amdgcn_update_dpp(0, v, kCtrl, kRows, 0xf, false);
+}
+template <class Step>
+__device__ __forceinline__ void wave_scan_steps(const Step &step) {
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+}
+__device__ __forceinline__ int64_t wave_scan(int64_t v) {
+    wave_scan_steps([&](auto ctrl, auto rows) {
+        const int32_t lo = lanes_moved<decltype(ctrl)::value, decltype(rows)::value>((int32_t)v);
+        const int32_t hi = lanes_moved<decltype(ctrl)::value, decltype(rows)::value>((int32_t)(v >> 32));
+        v += (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+    });
+    return v;
+}
+__device__ __forceinline__ int32_t wave_scan(int32_t v) {
+    wave_scan_steps([&](auto ctrl, auto rows) { v += lanes_moved<decltype(ctrl)::value, decltype(rows)::value>(v); });
+    return v;
+}
+__device__ __forceinline__ uint32_t wave_scan_max(uint32_t v) {
+    wave_scan_steps([&](auto ctrl, auto rows) {
+        v = max(v, (uint32_t)lanes_moved<decltype(ctrl)::value, decltype(rows)::value>((int32_t)v));
+    });
+    return v;
 }
 
 // The scan done inside the expansion (one-call sampling, and rays walked in
@@ -1111,16 +1141,13 @@ __device__ inline int64_t offset_of_ray(int64_t i, const ChunkScan &cs) {
 }
 
 // Inclusive block scan of x (returned, with its total) and the block sum of
-// y, sharing one exchange through LDS (lds holds 2 * kBlock / 64 entries).
+// y, sharing one exchange through LDS (lds holds 2 * kBlock / 64 entries, not
+// written again before a barrier).
 __device__ __forceinline__ int64_t block_scan_and_sum256(int64_t x, int64_t y, int64_t *lds, int64_t &x_total,
                                                         int64_t &y_total) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t a = __shfl_up(x, off, 64);
-        if (lane >= off) x += a;
-        y += __shfl_xor(y, off, 64);
-    }
+    x = wave_scan(x);
+    y = wave_scan(y);
     if (lane == 63) {
         lds[wid] = x;
         lds[kBlock / 64 + wid] = y;
@@ -1136,43 +1163,218 @@ __device__ __forceinline__ int64_t block_scan_and_sum256(int64_t x, int64_t y, i
         x_total += v;
         y_total += lds[kBlock / 64 + w];
     }
+    return below + x;
+}
+__device__ __forceinline__ int32_t block_scan256(int32_t x, int32_t *lds, int32_t &total) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    x = wave_scan(x);
+    if (lane == 63) lds[wid] = x;
     __syncthreads();
+    int32_t below = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) {
+        const int32_t v = lds[w];
+        if (w < wid) below += v;
+        total += v;
+    }
     return below + x;
 }
 
-// LDS of one expansion block, declared once per kernel so that the two
-// instantiations of expand_chunk share it.
+// A staged run: its first lattice index less its first output (mod 2^32: output
+// p has lattice index bn + p), and its ray (-1: a lost ray's placeholder).
+struct RunBody {
+    uint32_t bn;
+    int32_t ray;
+};
+
+// LDS of one expansion block.
 struct ExpandLds {
-    uint32_t start[kExpandRuns + 1];   // [cn] bounds the last run of the pass
-    uint32_t bn[kExpandRuns];          // n0 - start (mod 2^32): output j has lattice index bn + j
-    int32_t ray[kExpandRuns];          // -1: placeholder of a lost ray
-    int16_t scene[kExpandRuns];
+    uint32_t start[kExpandRuns + 1];   // first output; [cn] bounds the last run of the pass
+    RunBody body[kExpandRuns];
     uint32_t own[kOwnSlots];           // 1 + owner run of each group of the window, at own_slot(group)
     uint32_t wmax[kBlock / 64];
+    int32_t runs[kBlock / 64];
     int64_t wave[2 * (kBlock / 64)];
 };
 
-// kCone: some ray is on a growing-step lattice, whose points come from a table
-// in global memory.  Otherwise the write loop issues no load: a load there
-// would make every group wait for the stores of the one before (one counter
-// covers both on this architecture).
-template <bool kCone, bool kScan, class Lats>
-__device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float2 *s_lat, int64_t r0, int part,
+// Points of a lattice: computed (constant step, kTable false), or read from a
+// table in LDS or in global memory.
+template <bool kTable>
+struct Points {
+    float tmin, dt;
+    const float *tab;
+    int n_tab;
+    __device__ __forceinline__ void at(int n, float &a, float &b) const {
+        if constexpr (kTable) {
+            // outputs beside the written ones are looked up too
+            n = min(max(n, 0), n_tab - 2);
+            a = tab[n];
+            b = tab[n + 1];
+        } else {   // Lattice::t of a constant step
+            const float f = (float)n;
+            a = __fadd_rn(tmin, __fmul_rn(f, dt));
+            b = __fadd_rn(tmin, __fmul_rn(f + 1.0f, dt));
+        }
+    }
+};
+
+// What a block knows of its chunk.  Outputs are counted from the chunk's first
+// group of four (absolute output 4 * g0).
+struct ChunkOut {
+    int64_t g0;
+    uint32_t lim;          // outputs end here (chunk's end or capacity)
+    uint32_t end;          // the chunk's outputs end here
+    uint32_t start, len;   // the lane's row's outputs
+    int64_t row;
+    int32_t ray;
+    int nr;                // its runs to stage (kRunsLost: lost), 0 if the part needs none of it
+    int2 s0, s1;           // the first two
+};
+
+// Writes the outputs of the part's windows whose rows are `mine`; the others'
+// runs become placeholders.  Entered and left by the whole block.
+template <class P>
+__device__ __forceinline__ void expand_windows(ExpandLds &sh, const ChunkOut &ch, int part, bool mine,
+                                               const RunReader &rd, const P &pts, int32_t *__restrict__ ray_ids,
+                                               float *__restrict__ t0, float *__restrict__ t1, bool vec4) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int nr = ch.nr;
+    int32_t ray = ch.ray;
+    int2 s0 = ch.s0;
+    if (nr != 0 && (nr == kRunsLost || !mine)) {
+        nr = ch.len > 0 ? 1 : 0;
+        s0 = make_int2(0, (int)ch.len);
+        ray = -1;
+    }
+    for (int i = threadIdx.x; i < kOwnSlots; i += kBlock) sh.own[i] = 0;
+    int32_t total;
+    const int rb = block_scan256(nr, sh.runs, total) - nr;
+    uint32_t epoch = 0;   // window number within the block
+    for (int c0 = 0; c0 < total; c0 += kExpandRuns) {
+        const int cn = min(total - c0, kExpandRuns);
+        // stage runs c0 .. c0+cn-1; slot cn takes the next pass's first start.
+        uint32_t st = ch.start;
+        auto stage = [&](int k, int2 rn) {
+            const int idx = rb + k - c0;
+            if (idx >= 0 && idx <= cn) {
+                sh.start[idx] = st;
+                if (idx < cn) sh.body[idx] = RunBody{(uint32_t)rn.x - st, ray};
+            }
+            st += (uint32_t)(rn.y - rn.x);
+        };
+        if (nr > 0) stage(0, s0);
+        if (nr > 1) stage(1, ch.s1);
+        if (nr > 2) {   // two, then four at a time, their loads together
+            const int2 r2 = rd.slots[2 * rd.stride + ch.row], r3 = rd.slots[3 * rd.stride + ch.row];
+            stage(2, r2);
+            if (nr > 3) stage(3, r3);
+        }
+        int32_t chunk = -1;
+        for (int k = 4; k < nr; k += 4) {
+            const int2 *src = rd.slots + (int64_t)k * rd.stride + ch.row;
+            int64_t next = rd.stride;
+            if (k >= kMaxRuns) {
+                if (k % kMaxRuns == 0) chunk = k == kMaxRuns ? rd.ray_next[ch.row] : rd.chunk_next[chunk];
+                src = rd.chunks + (int64_t)chunk * kMaxRuns + k % kMaxRuns;
+                next = 1;
+            }
+            const int2 r0 = src[0], r1 = src[next], r2 = src[2 * next], r3 = src[3 * next];
+            stage(k, r0);
+            if (k + 1 < nr) stage(k + 1, r1);
+            if (k + 2 < nr) stage(k + 2, r2);
+            if (k + 3 < nr) stage(k + 3, r3);
+        }
+        if (threadIdx.x == 0 && c0 + cn == total) sh.start[cn] = ch.end;
+        __syncthreads();
+        const uint32_t lo = sh.start[0];
+        const uint32_t hi = min(sh.start[cn], ch.lim);
+        if (hi > lo) {
+            // groups covering [lo, hi)
+            const uint32_t g_first = lo >> 2, g_last = (hi - 1) >> 2;
+            // this part's windows that meet the pass: w = part, part + kExpandParts, ...
+            uint32_t w = g_first / kExpandGroups;
+            w += ((uint32_t)part - w) % kExpandParts;
+            for (; w * kExpandGroups <= g_last; w += kExpandParts) {
+                const uint32_t gw = max(g_first, w * kExpandGroups);
+                const int nwin = (int)(min(g_last, (w + 1) * kExpandGroups - 1) - gw + 1);
+                const uint32_t tag = ++epoch << kOwnerBits;
+                for (int a = threadIdx.x; a < cn; a += kBlock) {
+                    const uint32_t g = sh.start[a] >> 2;
+                    if (g >= gw + nwin) continue;
+                    // a run starting before the window marks group 0 if it is the last such run
+                    // (run 0 starts at or before gw, so group 0 always holds a mark of this window)
+                    if (g >= gw || a + 1 == cn || (sh.start[a + 1] >> 2) >= gw)
+                        atomicMax(&sh.own[own_slot(g > gw ? (int)(g - gw) : 0)], tag | (uint32_t)(a + 1));
+                }
+                __syncthreads();
+                // block-wide inclusive max-scan of own
+                uint32_t v[kGroupsPerLane];
+                uint32_t m = 0;
+#pragma unroll
+                for (int e = 0; e < kGroupsPerLane; ++e) {
+                    m = max(m, sh.own[(kGroupsPerLane + 1) * threadIdx.x + e]);
+                    v[e] = m;
+                }
+                const uint32_t incl = wave_scan_max(m);
+                if (lane == 63) sh.wmax[wid] = incl;
+                uint32_t pre = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x138, 0xf, 0xf, false);   // lane below
+                __syncthreads();
+                for (int q = 0; q < wid; ++q) pre = max(pre, sh.wmax[q]);
+#pragma unroll
+                for (int e = 0; e < kGroupsPerLane; ++e) sh.own[(kGroupsPerLane + 1) * threadIdx.x + e] = max(pre, v[e]);
+                __syncthreads();
+                // each lane writes groups k = tid, tid + 256, ... of the window
+                const int64_t at = 4 * (ch.g0 + gw);
+                int32_t *const wi = ray_ids + at;
+                float *const w0 = t0 + at, *const w1 = t1 + at;
+                for (int k = threadIdx.x; k < nwin; k += kBlock) {
+                    const int a = (int)(sh.own[own_slot(k)] & ((1u << kOwnerBits) - 1)) - 1;   // owns the group's last output
+                    const uint32_t p = 4 * (gw + (uint32_t)k);
+                    // runs a-1, a-2, a-3 may own the group's earlier outputs
+                    const uint32_t sa = sh.start[a], sb = sh.start[max(a - 1, 0)], sc = sh.start[max(a - 2, 0)];
+                    int4 id;
+                    float4 x0, x1;
+                    auto one = [&](uint32_t j, int32_t &r, float &u, float &v) {
+                        const RunBody b = sh.body[max(a - (int)(sa > j) - (int)(sb > j) - (int)(sc > j), 0)];
+                        r = b.ray;
+                        pts.at((int)(b.bn + j), u, v);
+                    };
+                    one(p, id.x, x0.x, x1.x);
+                    one(p + 1, id.y, x0.y, x1.y);
+                    one(p + 2, id.z, x0.z, x1.z);
+                    id.w = sh.body[a].ray;
+                    pts.at((int)(sh.body[a].bn + p + 3), x0.w, x1.w);
+                    if (vec4 && p >= lo && p + 3 < hi && (id.x | id.y | id.z | id.w) >= 0) {
+                        reinterpret_cast<int4 *>(wi)[k] = id;
+                        reinterpret_cast<float4 *>(w0)[k] = x0;
+                        reinterpret_cast<float4 *>(w1)[k] = x1;
+                    } else {   // an end, a placeholder, or no 16-byte stores
+                        const int q = 4 * k;
+                        if (p >= lo && p < hi && id.x >= 0) wi[q] = id.x, w0[q] = x0.x, w1[q] = x1.x;
+                        if (p + 1 >= lo && p + 1 < hi && id.y >= 0) wi[q + 1] = id.y, w0[q + 1] = x0.y, w1[q + 1] = x1.y;
+                        if (p + 2 >= lo && p + 2 < hi && id.z >= 0) wi[q + 2] = id.z, w0[q + 2] = x0.z, w1[q + 2] = x1.z;
+                        if (p + 3 >= lo && p + 3 < hi && id.w >= 0) wi[q + 3] = id.w, w0[q + 3] = x0.w, w1[q + 3] = x1.w;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        __syncthreads();
+    }
+    if (total == 0) __syncthreads();   // own and runs are free for the next use
+}
+
+template <bool kScan, class Lats>
+__device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float *table_lds, int64_t r0, int part,
                                              int64_t *__restrict__ offsets, const ChunkScan &cs, int64_t n_rays,
                                              const int32_t *__restrict__ nruns, const RunReader &rd,
                                              const Lats &lats, int64_t capacity, int32_t *__restrict__ ray_ids,
                                              float *__restrict__ t0, float *__restrict__ t1, bool vec4) {
-    uint32_t *const s_start = sh.start, *const s_bn = sh.bn, *const s_own = sh.own, *const s_wmax = sh.wmax;
-    int32_t *const s_ray = sh.ray;
-    int16_t *const s_scene = sh.scene;
-    int64_t *const s_wave = sh.wave;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t r = r0 + threadIdx.x;
     const bool in = r < n_rays;
     const int64_t rc = in ? r : n_rays - 1;   // lanes past the last ray load a valid one's
     int64_t base, bend, off, off_next;
-    int nr_rc;
-    int2 slot0, slot1;
     if constexpr (kScan) {
         // every load here depends on r alone and is issued in one round: the
         // sums before the chunk (whole tiles, then the earlier chunks of its
@@ -1191,7 +1393,7 @@ __device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float2 *s_lat,
         if (j < c) before += cs.chunk_sums[j];
         const int64_t cnt = in ? (int64_t)cs.counts[r] : 0;
         int64_t total;
-        const int64_t incl = block_scan_and_sum256(cnt, before, s_wave, total, base);
+        const int64_t incl = block_scan_and_sum256(cnt, before, sh.wave, total, base);
         off = base + incl - cnt;
         off_next = base + incl;
         bend = base + total;
@@ -1209,9 +1411,18 @@ __device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float2 *s_lat,
         bend = offsets[min(r0 + kBlock, n_rays)];
     }
     const int64_t lim = min(bend, capacity);
-    if (lim <= base) return;   // block-uniform: nothing to write
     const int64_t G0 = base >> 2;   // the chunk's first group; windows count from it
-    if ((((lim - 1) >> 2) - G0) / kExpandGroups < part) return;   // block-uniform: no window of this part
+    if (lim <= base || (((lim - 1) >> 2) - G0) / kExpandGroups < part) {   // block-uniform: nothing to write
+        if constexpr (kScan) __syncthreads();   // sh.wave is free for the next item
+        return;
+    }
+    ChunkOut ch;
+    ch.g0 = G0;
+    const int64_t origin = 4 * G0;
+    ch.lim = (uint32_t)(lim - origin);
+    ch.end = (uint32_t)(bend - origin);
+    ch.row = r;
+    ch.ray = (int32_t)(kScan ? r >> cs.parts_log2 : r);
     // Every other global load of the staging depends on r alone, so all of
     // them are issued here together: one memory round trip (the ray's offsets
     // and run count, and its first two run slots, read whether or not the ray
@@ -1219,12 +1430,11 @@ __device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float2 *s_lat,
     if constexpr (!kScan) {
         off = offsets[rc];
         off_next = offsets[rc + 1];
-        nr_rc = nruns[rc];
-        slot0 = rd.slots[rc];
-        slot1 = rd.slots[rd.stride + rc];
-    }
-    bool mine = in;
-    if constexpr (kScan) {
+        ch.nr = nruns[rc];
+        ch.s0 = rd.slots[rc];
+        ch.s1 = rd.slots[rd.stride + rc];
+        if (!in) ch.nr = 0;
+    } else {
         // With the offsets computed here, a part stages only the rays whose
         // outputs meet one of its windows (w = part, part + kExpandParts, ...),
         // and only those rays' run counts and first run slots are read: the
@@ -1232,156 +1442,37 @@ __device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float2 *s_lat,
         // This cuts the expansion's reads by more than half.  The three-call
         // form, whose offsets come from memory, measured slower with it and
         // keeps every ray.
-        mine = in && off_next > off;
-        if (mine) {
+        bool needed = in && off_next > off;
+        if (needed) {
             const int64_t wa = ((off >> 2) - G0) / kExpandGroups, wb = (((off_next - 1) >> 2) - G0) / kExpandGroups;
-            mine = wa + ((part - (int)(wa % kExpandParts)) + kExpandParts) % kExpandParts <= wb;
+            needed = wa + ((part - (int)(wa % kExpandParts)) + kExpandParts) % kExpandParts <= wb;
         }
-        nr_rc = 0;
-        slot0 = slot1 = make_int2(0, 0);
-        if (mine) {
-            nr_rc = nruns[rc];
-            slot0 = rd.slots[rc];
-            slot1 = rd.slots[rd.stride + rc];
+        ch.nr = 0;
+        ch.s0 = ch.s1 = make_int2(0, 0);
+        if (needed) {
+            ch.nr = nruns[rc];
+            ch.s0 = rd.slots[rc];
+            ch.s1 = rd.slots[rd.stride + rc];
         }
     }
-    const int nr_raw = mine ? nr_rc : 0;
-    const uint32_t end_rel = (uint32_t)(bend - base);
-    const uint32_t lim_rel = (uint32_t)(min(bend, capacity) - base);
-    int nr = nr_raw, scene = 0;
-    const bool lost = nr_raw == kRunsLost;
-    const uint32_t start = in ? (uint32_t)(off - base) : 0u;
-    const uint32_t lost_len = lost ? (uint32_t)(off_next - off) : 0u;
-    if (lost) nr = lost_len > 0 ? 1 : 0;
-    if (in) scene = lats.scene_of(r);
-    for (int i = threadIdx.x; i < kOwnSlots; i += kBlock) s_own[i] = 0;
-    int64_t total;
-    const int rb = (int)(block_incl_scan256((int64_t)nr, s_wave, total) - nr);
-    uint32_t epoch = 0;   // window number within the block
-    for (int c0 = 0; c0 < (int)total; c0 += kExpandRuns) {
-        const int cn = min((int)total - c0, kExpandRuns);
-        // stage runs c0 .. c0+cn-1; slot cn takes the next pass's first start.
-        uint32_t st = start;
-        int32_t chunk = -1;
-        const int2 *sp = rd.slots + r;
-        const int2 r0v = lost ? make_int2(0, (int)lost_len) : slot0, r1v = slot1;
-        for (int k = 0; k < nr; ++k) {
-            int2 rn = k == 0 ? r0v : r1v;
-            if (!lost && k >= 2) {
-                if (k < kMaxRuns) {
-                    rn = sp[(int64_t)k * rd.stride];
-                } else {
-                    if (k % kMaxRuns == 0) chunk = k == kMaxRuns ? rd.ray_next[r] : rd.chunk_next[chunk];
-                    rn = rd.chunks[(int64_t)chunk * kMaxRuns + k % kMaxRuns];
-                }
-            }
-            const int idx = rb + k - c0;
-            if (idx >= 0 && idx <= cn) s_start[idx] = st;
-            if (idx >= 0 && idx < cn) {
-                s_bn[idx] = (uint32_t)rn.x - st;
-                s_ray[idx] = lost ? -1 : (int32_t)(kScan ? r >> cs.parts_log2 : r);
-                s_scene[idx] = (int16_t)scene;
-            }
-            st += (uint32_t)(rn.y - rn.x);
-        }
-        if (threadIdx.x == 0 && c0 + cn == (int)total) s_start[cn] = end_rel;
-        __syncthreads();
-        const uint32_t lo = s_start[0];
-        const uint32_t hi = min(s_start[cn], lim_rel);
-        if (hi > lo) {
-            // absolute groups of 4 outputs covering [base + lo, base + hi)
-            const int64_t g_first = (base + lo) >> 2, g_last = (base + hi - 1) >> 2;
-            // this part's windows that meet the pass: w = part, part + kExpandParts, ...
-            int64_t w = (g_first - G0) / kExpandGroups;
-            w += ((part - (int)(w % kExpandParts)) + kExpandParts) % kExpandParts;
-            for (; G0 + w * kExpandGroups <= g_last; w += kExpandParts) {
-                const int64_t gw = max(g_first, G0 + w * kExpandGroups);
-                const int nwin = (int)(min(g_last, G0 + (w + 1) * kExpandGroups - 1) - gw + 1);
-                const uint32_t tag = ++epoch << kOwnerBits;
-                for (int a = threadIdx.x; a < cn; a += kBlock) {
-                    const int64_t g = ((base + s_start[a]) >> 2) - gw;
-                    if (g >= nwin) continue;
-                    // a run starting before the window marks group 0 if it is the last such run
-                    // (run 0 starts at or before gw, so group 0 always holds a mark of this window)
-                    if (g >= 0 || a + 1 == cn || ((base + s_start[a + 1]) >> 2) >= gw)
-                        atomicMax(&s_own[own_slot(g > 0 ? (int)g : 0)], tag | (uint32_t)(a + 1));
-                }
-                __syncthreads();
-                // block-wide inclusive max-scan of s_own
-                uint32_t v[kGroupsPerLane];
-                uint32_t m = 0;
-#pragma unroll
-                for (int e = 0; e < kGroupsPerLane; ++e) {
-                    m = max(m, s_own[(kGroupsPerLane + 1) * threadIdx.x + e]);
-                    v[e] = m;
-                }
-                uint32_t incl = m;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const uint32_t y = __shfl_up(incl, off, 64);
-                    if (lane >= off) incl = max(incl, y);
-                }
-                if (lane == 63) s_wmax[wid] = incl;
-                __syncthreads();
-                uint32_t pre = 0;
-                for (int q = 0; q < wid; ++q) pre = max(pre, s_wmax[q]);
-                const uint32_t below = __shfl_up(incl, 1, 64);
-                if (lane > 0) pre = max(pre, below);
-#pragma unroll
-                for (int e = 0; e < kGroupsPerLane; ++e) s_own[(kGroupsPerLane + 1) * threadIdx.x + e] = max(pre, v[e]);
-                __syncthreads();
-                // each lane writes groups k = tid, tid + 256, ... of the window
-                for (int k = threadIdx.x; k < nwin; k += kBlock) {
-                    const int a = (int)(s_own[own_slot(k)] & ((1u << kOwnerBits) - 1)) - 1;   // owns the group's last output
-                    const int64_t j4 = 4 * (gw + k) - base;       // block-relative, may lie below lo
-                    // runs a-1, a-2, a-3 may own the group's earlier outputs
-                    const uint32_t sa = s_start[a];
-                    const uint32_t sb = a >= 1 ? s_start[a - 1] : 0u;
-                    const uint32_t sc = a >= 2 ? s_start[a - 2] : 0u;
-                    int32_t id[4];
-                    float x0[4], x1[4];
-                    bool ok[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int64_t j = j4 + q;
-                        ok[q] = j >= (int64_t)lo && j < (int64_t)hi;
-                        const uint32_t ju = (uint32_t)j;
-                        const int aq = a - (int)(sa > ju) - (int)(a >= 1 && sb > ju) - (int)(a >= 2 && sc > ju);
-                        const int b = ok[q] ? aq : a;
-                        id[q] = s_ray[b];
-                        ok[q] = ok[q] && id[q] >= 0;
-                        const int n = (int)(s_bn[b] + ju);
-                        if constexpr (kCone) {
-                            const Lattice L = lats.get(s_scene[b]);
-                            x0[q] = ok[q] ? L.t(n) : 0.0f;
-                            x1[q] = ok[q] ? L.t(n + 1) : 0.0f;
-                        } else {   // Lattice::t of a constant step, from LDS or the arguments
-                            float2 c;
-                            if constexpr (Lats::kMulti) c = s_lat[s_scene[b]];
-                            else c = make_float2(lats.lat.tmin, lats.lat.dt);
-                            x0[q] = ok[q] ? __fadd_rn(c.x, __fmul_rn((float)n, c.y)) : 0.0f;
-                            x1[q] = ok[q] ? __fadd_rn(c.x, __fmul_rn((float)(n + 1), c.y)) : 0.0f;
-                        }
-                    }
-                    const int64_t at = base + j4;
-                    if (vec4 && ok[0] && ok[1] && ok[2] && ok[3]) {
-                        *reinterpret_cast<int4 *>(ray_ids + at) = make_int4(id[0], id[1], id[2], id[3]);
-                        *reinterpret_cast<float4 *>(t0 + at) = make_float4(x0[0], x0[1], x0[2], x0[3]);
-                        *reinterpret_cast<float4 *>(t1 + at) = make_float4(x1[0], x1[1], x1[2], x1[3]);
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            if (ok[q]) {
-                                ray_ids[at + q] = id[q];
-                                t0[at + q] = x0[q];
-                                t1[at + q] = x1[q];
-                            }
-                    }
-                }
-                __syncthreads();
-            }
-        }
-        __syncthreads();
+    ch.start = in ? (uint32_t)(off - origin) : 0u;
+    ch.len = in ? (uint32_t)(off_next - off) : 0u;
+    auto write = [&](bool mine, const Lattice &L, bool in_lds) {
+        if (!L.cone)
+            expand_windows(sh, ch, part, mine, rd, Points<false>{L.tmin, L.dt, nullptr, 0}, ray_ids, t0, t1, vec4);
+        else if (in_lds)
+            expand_windows(sh, ch, part, mine, rd, Points<true>{L.tmin, L.dt, table_lds, L.n_tab}, ray_ids, t0, t1,
+                           vec4);
+        else
+            expand_windows(sh, ch, part, mine, rd, Points<true>{L.tmin, L.dt, L.tab, L.n_tab}, ray_ids, t0, t1, vec4);
+    };
+    if constexpr (Lats::kMulti) {
+        // scene by scene: nearly every chunk lies in one
+        const int64_t r1 = min(r0 + kBlock, n_rays);
+        for (int sc = lats.scene_of(r0); sc < lats.n && lats.first[sc] < r1; ++sc)
+            write(r >= lats.first[sc] && r < lats.first[sc + 1], lats.lats[sc], false);
+    } else {
+        write(true, lats.lat, lats.lat.n_tab <= kTableLds);
     }
 }
 
@@ -1400,31 +1491,19 @@ template <bool kScan = false, class Lats>
 __device__ __forceinline__ void expand_block(int64_t *__restrict__ offsets, const ChunkScan &cs, int64_t n_rays,
                                              const int32_t *__restrict__ nruns, const RunReader &rd,
                                              const Lats &lats, int64_t capacity, int32_t *__restrict__ ray_ids,
-                                             float *__restrict__ t0, float *__restrict__ t1, bool vec4) {
+                                             float *__restrict__ t0, float *__restrict__ t1, bool vec4, float *table_lds) {
     __shared__ ExpandLds sh;
-    __shared__ float2 s_lat[Lats::kMulti ? kBlock : 1];   // (tmin, dt) of every scene
-    bool cone;
-    if constexpr (Lats::kMulti) {
-        bool c = false;
-        if ((int)threadIdx.x < lats.n) {
-            const Lattice L = lats.get(threadIdx.x);
-            s_lat[threadIdx.x] = make_float2(L.tmin, L.dt);
-            c = L.cone;
+    if constexpr (!Lats::kMulti) {
+        const Lattice &L = lats.lat;
+        if (L.cone && L.n_tab <= kTableLds) {
+            for (int i = threadIdx.x; i < L.n_tab; i += kBlock) table_lds[i] = L.tab[i];
+            __syncthreads();
         }
-        cone = __syncthreads_or(c) != 0;
-    } else {
-        cone = lats.lat.cone;
     }
     const int64_t chunks = (n_rays + kBlock - 1) / kBlock;
-    if (cone) {
-        for (int64_t it = blockIdx.x; it < chunks * kExpandParts; it += gridDim.x)
-            expand_chunk<true, kScan>(sh, s_lat, it % chunks * kBlock, (int)(it / chunks), offsets, cs, n_rays, nruns,
-                                      rd, lats, capacity, ray_ids, t0, t1, vec4);
-    } else {
-        for (int64_t it = blockIdx.x; it < chunks * kExpandParts; it += gridDim.x)
-            expand_chunk<false, kScan>(sh, s_lat, it % chunks * kBlock, (int)(it / chunks), offsets, cs, n_rays,
-                                       nruns, rd, lats, capacity, ray_ids, t0, t1, vec4);
-    }
+    for (int64_t it = blockIdx.x; it < chunks * kExpandParts; it += gridDim.x)
+        expand_chunk<kScan>(sh, table_lds, it % chunks * kBlock, (int)(it / chunks), offsets, cs, n_rays, nruns, rd,
+                            lats, capacity, ray_ids, t0, t1, vec4);
 }
 
 // ------------------------------------------------------------------ ray order
