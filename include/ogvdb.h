@@ -202,7 +202,8 @@ ogv_status ogv_grid_refresh_density(ogv_grid *grid, float *cache_dev, const floa
 
 /* Workspace bytes a sample call needs for n_rays rays and this lattice: about
  * 152 B a ray, and for calls of up to 262,144 rays, which walk a ray in up to
- * 16 parts, that for each part (at most 40 MB).
+ * 16 parts, that for each part (at most 80 MB; ogv_sample_rays, which needs
+ * its workspace for one call only, also runs with less, down to 152 B a ray).
  * With a growing step (OGV_STEP_CONE) the workspace also keeps the lattice's
  * point table between calls, beside a header with near, far, cone, dt_min,
  * the table's length and a 64-bit hash of its entries.  A call on the same

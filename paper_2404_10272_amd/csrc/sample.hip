@@ -314,8 +314,9 @@ struct Plan {
     int32_t tab_cap;
 };
 
-bool make_plan(int64_t rays, float near_t, float far_t, const ogv_step *step, Plan *p, std::string *why) {
-    p->parts_log2 = parts_log2_of(rays);
+bool make_plan(int64_t rays, float near_t, float far_t, const ogv_step *step, int parts_log2, Plan *p,
+               std::string *why) {
+    p->parts_log2 = parts_log2;
     const int64_t n_rays = rays << p->parts_log2;
     p->n_rays = n_rays;
     p->n_tiles = scan_tiles(n_rays);
@@ -577,12 +578,19 @@ ogv_status check_voxel_ids(const ogv_grid *grid, const int32_t *vox, const char 
 
 ogv_status prepare(const ogv_grid *grid, const ogv_sample_opts &opts, const float *o, const float *d, int64_t n,
                    float near_t, float far_t, const ogv_step *step, void *ws, size_t ws_bytes, Plan *p,
-                   const char *fn) {
+                   const char *fn, bool one_call = false) {
     ogv_status st = validate_sampling(grid, opts.variant, o, d, n, near_t, far_t, step, fn);
     if (st != OGV_OK) return st;
     if (opts.image_width < 0) OGV_FAIL(OGV_ERR_INVALID, std::string(fn) + ": image_width < 0");
     std::string why;
-    if (!make_plan(n, near_t, far_t, step, p, &why)) OGV_FAIL(OGV_ERR_UNSUPPORTED, why);
+    p->parts_log2 = parts_log2_of(n);
+    if (!make_plan(n, near_t, far_t, step, p->parts_log2, p, &why)) OGV_FAIL(OGV_ERR_UNSUPPORTED, why);
+    // one call alone may take fewer parts than its size asks for, down to whole
+    // rays, if that is what its workspace holds (the fixed scratch array's
+    // 64 MiB are short of four parts for 131,072 rays); calls that follow each
+    // other on a workspace have to agree, and none knows the others' bytes
+    while (one_call && p->parts_log2 > 0 && ws_bytes < p->total)
+        make_plan(n, near_t, far_t, step, p->parts_log2 - 1, p, &why);
     if (!ws || ws_bytes < p->total)
         OGV_FAIL(OGV_ERR_CAPACITY, std::string(fn) + ": workspace smaller than ogv_sample_workspace_size");
     return OGV_OK;
@@ -599,7 +607,7 @@ extern "C" ogv_status ogv_sample_workspace_size(int64_t n_rays, float near_t, fl
     if (n_rays < 0) OGV_FAIL(OGV_ERR_INVALID, "n_rays < 0");
     Plan p;
     std::string why;
-    if (!make_plan(n_rays, near_t, far_t, step, &p, &why)) OGV_FAIL(OGV_ERR_UNSUPPORTED, why);
+    if (!make_plan(n_rays, near_t, far_t, step, parts_log2_of(n_rays), &p, &why)) OGV_FAIL(OGV_ERR_UNSUPPORTED, why);
     *bytes = p.total;
     return OGV_OK;
 }
@@ -643,7 +651,7 @@ extern "C" ogv_status ogv_sample_scan(int64_t n, int64_t *offsets, void *ws, siz
     const ogv_step unit{OGV_STEP_CONST, 1.0f, 0.0f, 0.0f};
     Plan p;
     std::string why;
-    if (!make_plan(n, 0.0f, 0.0f, &unit, &p, &why)) OGV_FAIL(OGV_ERR_UNSUPPORTED, why);
+    if (!make_plan(n, 0.0f, 0.0f, &unit, parts_log2_of(n), &p, &why)) OGV_FAIL(OGV_ERR_UNSUPPORTED, why);
     if (!ws || ws_bytes < p.off_tab) OGV_FAIL(OGV_ERR_CAPACITY, "workspace smaller than the count call's");
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) {
@@ -679,7 +687,7 @@ extern "C" ogv_status ogv_sample_rays(const ogv_grid *grid, const ogv_sample_opt
                                       int32_t *vox, int32_t *overflow, void *ws, size_t ws_bytes, void *stream) {
     const ogv_sample_opts opts = opts_of(opts_p);
     Plan p;
-    ogv_status st = prepare(grid, opts, o, d, n, near_t, far_t, step, ws, ws_bytes, &p, "ogv_sample_rays");
+    ogv_status st = prepare(grid, opts, o, d, n, near_t, far_t, step, ws, ws_bytes, &p, "ogv_sample_rays", true);
     if (st != OGV_OK) return st;
     if (!offsets || !overflow) OGV_FAIL(OGV_ERR_INVALID, "offsets/overflow is null");
     if (capacity < 0) OGV_FAIL(OGV_ERR_INVALID, "capacity < 0");
@@ -745,7 +753,7 @@ extern "C" ogv_status ogv_sample_rays_noalloc(const ogv_grid *grid, const ogv_sa
     if (n < 0) OGV_FAIL(OGV_ERR_INVALID, "ogv_sample_rays_noalloc: n_rays < 0");
     Plan p;
     std::string why;
-    if (!make_plan(n, near_t, far_t, step, &p, &why)) OGV_FAIL(OGV_ERR_UNSUPPORTED, why);
+    if (!make_plan(n, near_t, far_t, step, 0, &p, &why)) OGV_FAIL(OGV_ERR_UNSUPPORTED, why);   // the least it takes
     if (p.total > (size_t)OGV_NOALLOC_SCRATCH_BYTES)
         OGV_FAIL(OGV_ERR_CAPACITY, "ogv_sample_rays_noalloc: the call needs " + std::to_string(p.total) +
                                        " bytes of workspace, more than the " +
