@@ -418,9 +418,9 @@ struct Blobs {
 // as matrix instructions ignore the lane mask.
 //
 // Bound by VALU issue, the exponentials' quarter rate first: 640,000 rays of 25.4 M
-// samples through 12 blobs take 184 us.  Twelve instructions a blob and sample
+// samples through 12 blobs take 191 us.  Twelve instructions a blob and sample
 // and a ray a row took 311 us; the form below with a ray a row 265.
-constexpr int kWaveRays = 16;
+constexpr int kWaveRays = 8;
 struct RenderLds {
     float2 uw[kWaveRays][kRow];        // u_k, W_k of each ray with samples
     float2 ref_scale[kWaveRays];       // its reference parameter and |d|
@@ -574,24 +574,30 @@ __global__ void __launch_bounds__(kBlock) render_blobs_kernel(const int64_t *__r
     }
     wave_fence();
     if (!live) return;
-    // lane i again: its ray's parts, from the back
-    float C[4] = {0.f, 0.f, 0.f, 0.f};
+    // lane i again: its ray's parts, from the back, in 64 bits so that a cut
+    // costs no rounding of its own
+    double C[4] = {0., 0., 0., 0.};
     if (chunks > 0) {
 #pragma unroll
         for (int q = 3; q >= 0; --q) {
             const int32_t from = (int32_t)((int64_t)total * q / 4), upto = (int32_t)((int64_t)total * (q + 1) / 4);
             if (max(from, last - chunks) >= min(upto, last)) continue;
             const float *p = w.part[slot][q];
-            const float T = exp_neg(p[0]);
+            if (upto >= last) {   // the ray's last part
 #pragma unroll
-            for (int k = 0; k < 4; ++k) C[k] = fmaf(T, C[k], p[1 + k]);
+                for (int k = 0; k < 4; ++k) C[k] = p[1 + k];
+            } else {
+                const double T = exp2_64(fmin(-1.4426950408889634 * (double)p[0], 1000.));
+#pragma unroll
+                for (int k = 0; k < 4; ++k) C[k] = fma(T, C[k], (double)p[1 + k]);
+            }
         }
     }
     const int64_t r = r0 + lane;
-    out_rgb[3 * r + 0] = C[0];
-    out_rgb[3 * r + 1] = C[1];
-    out_rgb[3 * r + 2] = C[2];
-    if (out_opacity) out_opacity[r] = C[3];
+    out_rgb[3 * r + 0] = (float)C[0];
+    out_rgb[3 * r + 1] = (float)C[1];
+    out_rgb[3 * r + 2] = (float)C[2];
+    if (out_opacity) out_opacity[r] = (float)C[3];
 }
 
 }  // namespace
@@ -653,10 +659,13 @@ extern "C" ogv_status ogv_render_blobs(const int64_t *offsets, int64_t n_rays, c
     if (n_rays == 0) return OGV_OK;
     if (!offsets || !origins || !dirs || !t0 || !t1 || !out_rgb) OGV_FAIL(OGV_ERR_INVALID, "null argument");
     hipStream_t s = (hipStream_t)stream;
-    // 16 rays a wave even their lengths out best (300,000 rays 53.7 us against
-    // 55.4 with 8); calls of fewer rays need the waves instead (100,000 rays
-    // 92 us with 4 against 113 with 16, 20,000 17 against 27)
-    const int per = n_rays >= 262144 ? kWaveRays : n_rays >= 131072 ? 8 : 4;
+    // 8 rays a wave even their lengths out (640,000 rays of random lengths 191 us
+    // against 215 with 4) and still part the long rays of an image's middle
+    // (800x800 rays of one object 170 us, with 4 rays 175; 16 take 187 on the
+    // random lengths and 190 here).  Calls of fewer rays need the waves instead:
+    // half that image 96 us with 4 against 101 with 8, a quarter 57 against 68,
+    // 300,000 random rays 108 against 99
+    const int per = n_rays >= 524288 ? kWaveRays : 4;
     const int64_t per_block = (int64_t)per * (kBlock / 64);
     const unsigned blocks = (unsigned)((n_rays + per_block - 1) / per_block);
     // one instantiation per number of blobs: a blob's row broadcast is part of

@@ -53,7 +53,7 @@ def test_every_number_of_blobs_and_lengths_around_chunks(blobs):
         _check(counts, *_rays(n, rng), *_steps(int(counts.sum()), rng), _field(blobs, rng))
 
 
-@pytest.mark.parametrize("n", [131071, 131072, 262143, 262144, 262161])
+@pytest.mark.parametrize("n", [131071, 131072, 262143, 262144, 262161, 524287, 524288, 524297])
 def test_ray_counts_around_the_waves_shares(n):
     rng = np.random.default_rng(9520)
     counts = rng.choice([0, 0, 1, 2, 7, 20], n)
