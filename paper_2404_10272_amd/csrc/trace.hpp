@@ -1469,8 +1469,12 @@ __device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float *table_l
     if constexpr (Lats::kMulti) {
         // scene by scene: nearly every chunk lies in one
         const int64_t r1 = min(r0 + kBlock, n_rays);
-        for (int sc = lats.scene_of(r0); sc < lats.n && lats.first[sc] < r1; ++sc)
-            write(r >= lats.first[sc] && r < lats.first[sc + 1], lats.lats[sc], false);
+        for (int sc = lats.scene_of(r0); sc < lats.n && lats.first[sc] < r1; ++sc) {
+            const Lattice L = lats.lats[sc];
+            // a growing step with far < near has no table to look points up in, and its rays no samples
+            if (L.cone && L.n_tab == 0) continue;
+            write(r >= lats.first[sc] && r < lats.first[sc + 1], L, false);
+        }
     } else {
         write(true, lats.lat, lats.lat.n_tab <= kTableLds);
     }
