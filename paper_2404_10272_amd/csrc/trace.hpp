@@ -969,21 +969,24 @@ __device__ __forceinline__ void trace_ray(const GridView &g, const Tree &tree, c
             meet_level(g, lev, ray, at);
             a = k <= m ? at.E : in.X;
             b = k < m ? in.E : at.X;
-            bool starts = true;
             if (part.n > 1) {
+                // Both parts beside a boundary w get the same cut of the segment
+                // from it, and cuts rise with w: whatever the lengths and their
+                // rounding are, each parameter falls to one part.  A segment
+                // that adds nothing to `done` (no length inside [t_min, t_max],
+                // as every one of a ray with near = far) goes whole to one part.
                 const float t0 = clip(a), len = __fsub_rn(clip(b), t0), here = __fmul_rn(len, density(lev));
                 const float before = done, next = __fadd_rn(done, here);
-                const auto c = [&](float w) {
-                    return fminf(fmaxf(__fadd_rn(t0, __fmul_rn(len, (w - before) / here)), a), b);
+                const auto cut = [&](float w) {
+                    if (w <= before) return a;
+                    return w < next ? fminf(fmaxf(__fadd_rn(t0, __fmul_rn(len, (w - before) / here)), a), b) : b;
                 };
-                const bool last = part.j + 1 == part.n;
-                starts = (part.j == 0 || from < next) && (last || to > before);
-                const float a_part = part.j > 0 && from > before ? c(from) : a;
-                b = !last && to < next ? c(to) : b;
+                const float a_part = part.j > 0 ? cut(from) : a;
+                b = part.j + 1 < part.n ? cut(to) : b;
                 a = a_part;
                 done = next;
             }
-            found = starts && a < b && b >= lat.tmin && a < lat.tmax;
+            found = a < b && b >= lat.tmin && a < lat.tmax;
         }
         if (found) march_segment<kGrid, kSkip>(g, tree, lev, ray, at, a, b, lat, vis, ctx);
     }
