@@ -905,15 +905,21 @@ struct RayPart {
 //
 // The parts share a ray's range evenly by the voxels it crosses: over one
 // level evenly in t, over cascades by length over voxel size.
+
+// Clips the span (a, b] of a one-level ray to a part of it.
+__device__ __forceinline__ void clip_to_part(RayPart part, const Lattice &lat, float &a, float &b) {
+    const float t0 = fmaxf(a, lat.tmin), len = __fsub_rn(fminf(b, lat.tmax), t0), each = 1.0f / (float)part.n;
+    const auto c = [&](int j) { return __fadd_rn(t0, __fmul_rn(len, __fmul_rn((float)j, each))); };
+    if (part.j > 0) a = fmaxf(a, c(part.j));
+    if (part.j + 1 < part.n) b = fminf(b, c(part.j + 1));
+}
+
 template <int kGrid, bool kSkip, class Vis, class Ctx>
 __device__ __forceinline__ void march_l1(const GridView &g, const Tree &tree, const L1Span &s, RayPart part,
                                          const Lattice &lat, Vis &vis, const Ctx &ctx) {
     float a = s.m.E, b = s.m.X;
     if (part.n > 1) {
-        const float t0 = fmaxf(a, lat.tmin), len = __fsub_rn(fminf(b, lat.tmax), t0), each = 1.0f / (float)part.n;
-        const auto c = [&](int j) { return __fadd_rn(t0, __fmul_rn(len, __fmul_rn((float)j, each))); };
-        if (part.j > 0) a = fmaxf(a, c(part.j));
-        if (part.j + 1 < part.n) b = fminf(b, c(part.j + 1));
+        clip_to_part(part, lat, a, b);
         if (!(a < b)) return;
     }
     march_segment<kGrid, kSkip>(g, tree, 0, s.ray, s.m, a, b, lat, vis, ctx);
@@ -969,7 +975,11 @@ __device__ __forceinline__ void trace_ray(const GridView &g, const Tree &tree, c
             meet_level(g, lev, ray, at);
             a = k <= m ? at.E : in.X;
             b = k < m ? in.E : at.X;
-            if (part.n > 1) {
+            if (part.n > 1 && L == 1) {
+                // as the walk of one-level grids cuts it, to the bit: a part
+                // counted there may be walked again here
+                clip_to_part(part, lat, a, b);
+            } else if (part.n > 1) {
                 // Both parts beside a boundary w get the same cut of the segment
                 // from it, and cuts rise with w: whatever the lengths and their
                 // rounding are, each parameter falls to one part.  A segment

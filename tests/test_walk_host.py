@@ -109,3 +109,21 @@ def test_parts_cover_a_cascade_ray_once(walk, parts):
             d = np.asarray([1.0, 0.0, 0.0], np.float32)
         near, far = np.float32(0.1 * (k % 3)), np.float32([3.0, 9.0, 100.0][k % 3])
         _same_inside(runs_of(walk, g, o, d, near, far), in_parts(walk, g, o, d, near, far, parts), near, far, k)
+
+
+@pytest.mark.parametrize("R", [100, 128, 250])
+def test_both_walks_cut_a_one_level_ray_alike(walk, R):
+    """A part counted by the walk of one-level grids is walked again, when its
+    runs were lost, by the walk of any number of levels."""
+    rng = np.random.default_rng(9835)
+    g = Grid(np.ones((1, R, R, R)), [[-1.5] * 3 + [1.5] * 3])
+    for k in range(100):
+        o = rng.uniform(-4.0, 4.0, 3).astype(np.float32)
+        d = (rng.uniform(-1.4, 1.4, 3) - o).astype(np.float32)
+        n = 2 ** int(rng.integers(1, 5))
+        near, far = [(0.0, 8.0), (0.4, 0.9), (0.5, 0.5)][k % 3]
+        for j in range(n):
+            # runs behind far hold no samples, and either walk may leave them out
+            one, any_level = ([tuple(r) for r in runs_of(walk, g, o, d, near, far, (j, n), single) if r[0] < far]
+                              for single in (True, False))
+            assert one == any_level, (k, j, n)
