@@ -79,10 +79,10 @@ __global__ void pool_reset_kernel(int32_t *head, int64_t *tile_sums, int64_t n_t
 // blocks stride through their list, reading the tree from global memory.
 // Those outputs are disjoint from the expansion's (it skips them, and a
 // 16-byte group they share is written with 4-byte stores).
-// kScan: the offsets are not given but written here (ChunkScan), from the
-// count pass's counts and group sums: a one-call pass then needs no scan
-// launch.  The lost rays' first outputs then come from the sums too (the
-// offsets array is being written by other blocks of the same launch).
+// kScan: the rows' offsets are derived here (ChunkScan), in a one-call pass from
+// the count pass's counts and group sums, so that it needs no scan launch.  The
+// lost rays' first outputs then come from the sums too (the offsets array is
+// being written by other blocks of the same launch).
 template <int kGrid, bool kSkip, bool kScan>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kExpandWaves))) expand_kernel(GridView g, const float *__restrict__ origins,
                                                         const float *__restrict__ dirs,
@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kEx
     const FillCtx ctx{lat, capacity, ray_ids, t0, t1, nullptr, g.R};
     for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < m; k += (int64_t)gridDim.x * kBlock) {
         const int64_t row = lost[k];
-        const int64_t first = kScan ? offset_of_ray(row, cs) : offsets[row];
+        const int64_t first = kScan ? offset_of_row(row, cs, offsets) : offsets[row];
         if (first >= capacity) continue;
         const int sh = kScan ? cs.parts_log2 : 0;
         const int64_t i = row >> sh;
@@ -514,9 +514,9 @@ ogv_status count_and_scan(const ogv_grid *grid, int32_t variant, int width, cons
 }
 
 // The expansion of the runs the count pass left in the workspace.  scan: the
-// rows' offsets come from the count pass's counts and sums, and write says
-// whether the offsets array and the overflow flag are written; else they are
-// read from the offsets array.
+// rows' offsets come from the count pass's counts, beginning at its sums (write:
+// the offsets array and the overflow flag are written) or at the offsets given;
+// else they are read from the offsets array.
 ogv_status expand(const ogv_grid *grid, int32_t variant, const float *o, const float *d, int64_t *offsets, bool scan,
                   bool write, int64_t cap, int32_t *ids, float *t0, float *t1, int32_t *overflow, const Lattice &lat,
                   const Bufs &b, hipStream_t s) {

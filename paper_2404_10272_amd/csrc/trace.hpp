@@ -1128,10 +1128,12 @@ __device__ __forceinline__ uint32_t wave_scan_max(uint32_t v) {
 
 // The scan done inside the expansion (one-call sampling, and rays walked in
 // parts, whose rows the offsets array does not list): every block derives
-// its 256-row chunk's offsets from the count pass's per-ray counts and its
-// sums per 4096-ray scan tile and per 256-ray chunk, and the first part of
-// every chunk writes them to the offsets array (the last chunk also the total
-// and the overflow flag).  counts == nullptr: the offsets array is read.
+// its 256-row chunk's offsets from the count pass's per-ray counts, counted
+// from its sums per 4096-ray scan tile and per 256-ray chunk, and the first part
+// of every chunk writes them to the offsets array (the last chunk also the total
+// and the overflow flag); or, with the rays' offsets given (write == 0), counted
+// from the given offset of the chunk's first ray, so that a fill writes where its
+// offsets say.
 constexpr int kChunksPerTile = kScanTile / kBlock;
 struct ChunkScan {
     const int32_t *counts;       // [n_rays] (rows)
@@ -1139,17 +1141,23 @@ struct ChunkScan {
     const int64_t *chunk_sums;   // [ceil(n_rays / kBlock)]
     int32_t *overflow;           // nullable: set to (total > capacity)
     int32_t parts_log2;          // log2 of a ray's rows: the rows of ray i are i << parts_log2 ...
-    int32_t write;               // 0: the offsets array is not written (it already holds them)
+    int32_t write;               // 0: the offsets array is given, and not written
 };
 
-// First output of ray i from the sums (for the rare rays the count pass could
-// not keep runs for; a plain sequential sum).
-__device__ inline int64_t offset_of_ray(int64_t i, const ChunkScan &cs) {
-    const int64_t c = i / kBlock, T = i / kScanTile;
-    int64_t s = 0;
-    for (int64_t k = 0; k < T; ++k) s += cs.tile_sums[k];
-    for (int64_t j = T * kChunksPerTile; j < c; ++j) s += cs.chunk_sums[j];
-    for (int64_t r = c * kBlock; r < i; ++r) s += cs.counts[r];
+// First output of row i (for the rare rows the count pass could not keep runs
+// for; a plain sequential sum): from the sums, or, where the offsets are given,
+// from its ray's and the counts of the ray's rows before it.
+__device__ inline int64_t offset_of_row(int64_t i, const ChunkScan &cs, const int64_t *offsets) {
+    int64_t s = 0, r = i / kBlock * kBlock;
+    if (cs.write != 0) {
+        const int64_t c = i / kBlock, T = i / kScanTile;
+        for (int64_t k = 0; k < T; ++k) s += cs.tile_sums[k];
+        for (int64_t j = T * kChunksPerTile; j < c; ++j) s += cs.chunk_sums[j];
+    } else {
+        r = i >> cs.parts_log2 << cs.parts_log2;
+        s = offsets[i >> cs.parts_log2];
+    }
+    for (; r < i; ++r) s += cs.counts[r];
     return s;
 }
 
@@ -1401,9 +1409,13 @@ __device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float *table_l
             if ((cs.chunk_sums[c] + 6) / 4 <= (int64_t)part * kExpandGroups) return;
         }
         int64_t before = 0;
-        for (int64_t k = threadIdx.x; k < T; k += kBlock) before += cs.tile_sums[k];
-        const int64_t j = T * kChunksPerTile + threadIdx.x;
-        if (j < c) before += cs.chunk_sums[j];
+        if (cs.write != 0) {
+            for (int64_t k = threadIdx.x; k < T; k += kBlock) before += cs.tile_sums[k];
+            const int64_t j = T * kChunksPerTile + threadIdx.x;
+            if (j < c) before += cs.chunk_sums[j];
+        } else if (threadIdx.x == 0) {
+            before = offsets[r0 >> cs.parts_log2];   // a chunk's rows are those of whole rays
+        }
         const int64_t cnt = in ? (int64_t)cs.counts[r] : 0;
         int64_t total;
         const int64_t incl = block_scan_and_sum256(cnt, before, sh.wave, total, base);
