@@ -200,10 +200,13 @@ ogv_status ogv_grid_refresh(ogv_grid *grid, const uint8_t *occ_dev, void *stream
 ogv_status ogv_grid_refresh_density(ogv_grid *grid, float *cache_dev, const float *density_dev, float decay,
                                     float threshold, int32_t *changed_dev, void *stream);
 
-/* Workspace bytes a sample call needs for n_rays rays and this lattice: about
- * 152 B a ray, and for calls of up to 262,144 rays, which walk a ray in up to
- * 16 parts, that for each part (at most 80 MB; ogv_sample_rays, which needs
- * its workspace for one call only, also runs with less, down to 152 B a ray).
+/* Workspace bytes a sample call of up to n_rays rays needs on this lattice
+ * (the size never falls as n_rays grows): about 152 B a ray, and for calls of up
+ * to 262,144 rays, which walk a ray in up to 16 parts, that for each part, so
+ * that beyond 16,384 rays 40 MB and beyond 131,071 rays 80 MB is the least it
+ * reports.  ogv_sample_rays, which needs its workspace for one call only, also
+ * runs with less, down to about 152 B a ray; calls that follow each other on a
+ * workspace (count, scan, fill) need what this reports for their n_rays.
  * With a growing step (OGV_STEP_CONE) the workspace also keeps the lattice's
  * point table between calls, beside a header with near, far, cone, dt_min,
  * the table's length and a 64-bit hash of its entries.  A call on the same
