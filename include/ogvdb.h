@@ -275,8 +275,10 @@ ogv_status ogv_sample_rays(const ogv_grid *grid, const ogv_sample_opts *opts, co
  * argument.  The call allocates nothing; the caller still passes every input
  * and output, with the meaning ogv_sample_rays gives them.  The array is
  * reserved on each device the library runs on and held until the process
- * ends.  A call whose workspace (ogv_sample_workspace_size) exceeds it --
- * about 440,000 rays at a constant step -- fails with OGV_ERR_CAPACITY and
+ * ends.  Rays are walked in as many parts as it has room for.  A call whose
+ * whole rays do not fit it -- 152 B each with the run pool, and 4 B a point of a
+ * growing step: about 440,000 rays at a constant step, whatever
+ * ogv_sample_workspace_size reports -- fails with OGV_ERR_CAPACITY and
  * does nothing.  All calls on one device share its array: calls that
  * overlap in time on one device (other host threads, other streams) race,
  * so the caller orders them, e.g. on one stream. */
