@@ -49,10 +49,19 @@ __device__ __forceinline__ float row_suffix(float x) {
     x += dpp<0x108>(x);
     return x;
 }
+// smallest value of the row, in every lane (a lane whose source falls outside
+// the row keeps its own)
+template <int kCtrl>
+__device__ __forceinline__ float dpp_min(float x) {
+    return fminf(x, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), kCtrl, 0xF, 0xF, false)));
+}
 // value of lane kLane (0..15) of this lane's row
 template <int kLane>
 __device__ __forceinline__ float row_bcast(float x) {
     return dpp<0x150 + kLane>(x);
+}
+__device__ __forceinline__ float row_min(float x) {
+    return row_bcast<kRow - 1>(dpp_min<0x118>(dpp_min<0x114>(dpp_min<0x112>(dpp_min<0x111>(x)))));
 }
 
 // Each lane takes kPer consecutive samples of its row's ray, so a row covers
@@ -393,7 +402,11 @@ typedef float Acc __attribute__((ext_vector_type(4)));
 // a row holds u_k and W_k of its ray, in 64 bits up to their rounding, and every
 // lane of the row reads them with the instruction that uses them (DPP).  The
 // reference point lies among the blobs: s and u_k are small there and lose
-// nothing to the camera's distance, which o + d t rounded at does.
+// nothing to the camera's distance, which o + d t rounded at does.  It is the
+// mean of the nearest parameters of the blobs that the ray meets (W_k > 0), those
+// behind the origin or beyond twice the first one's left out: a blob far from the
+// others, or one without density, takes no bits from them, and samples near any
+// blob are no further from the reference than from the origin.
 template <int kK, int kN>
 struct Blobs {
     static __device__ __forceinline__ void add(const BlobArgs &f, const float channel[kN], float s, float u, float W,
@@ -499,10 +512,13 @@ __global__ void __launch_bounds__(kBlock) render_blobs_kernel(const int64_t *__r
             const double px = fma(dx, tc, ex), py = fma(dy, tc, ey), pz = fma(dz, tc, ez);
             const double arg = fma(px, px, fma(py, py, pz * pz)) * f.nk64[l];
             W = l < kN ? (float)(f.a[l] * exp2_64(arg)) : 0.f;
-            tc_f = l < kN ? (float)tc : 0.f;
+            tc_f = W > 0.f ? (float)tc : 0.f;
         }
-        ref = row_bcast<kRow - 1>(row_prefix(tc_f)) * (1.f / kN);
-        if (!(fabsf(ref) < 1e6f)) ref = 0.f;   // a direction so short that the blobs are nowhere near in t
+        const float first = row_min(tc_f > 0.f ? tc_f : __builtin_huge_valf());
+        const bool counts = tc_f > 0.f && tc_f <= 2.f * first;
+        const int met = __popcll(__ballot(counts) >> (lane & 48) & 0xffff);
+        ref = row_bcast<kRow - 1>(row_prefix(counts ? tc_f : 0.f)) * __builtin_amdgcn_rcpf((float)max(met, 1));
+        if (!__builtin_isfinite(ref)) ref = 0.f;   // a direction so short that the blobs are nowhere near in t
         u = (float)((tc - (double)ref) * len);
         if (ok) {
             w.uw[i][l] = make_float2(u, W);
