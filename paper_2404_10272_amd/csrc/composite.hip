@@ -567,8 +567,10 @@ __global__ void __launch_bounds__(kBlock) render_blobs_kernel(const int64_t *__r
         Acc sum = {0.f, 0.f, 0.f, 0.f};
         Blobs<0, kN>::add(f, channel, s, u, W, sum);
         const float sig = sum[0];
+        // the hardware's reciprocal, refined; it gives 0 where that would be no normal number
         float inv = __builtin_amdgcn_rcpf(sig);
-        inv = sig > 1e-30f ? fmaf(fmaf(-sig, inv, 1.f), inv, inv) : 0.f;
+        inv = sig >= 0x1p-126f ? fmaf(fmaf(-sig, inv, 1.f), inv, inv) : 0.f;
+        if (__any(sig > 0x1p125f)) inv = sig > 0x1p125f ? 1.f / sig : inv;
         const float tau = ok ? sig * dt : 0.f;
         const float incl = row_prefix(tau);
         const float wt = exp_neg(depth + dpp<0x111>(incl)) * alpha_of(tau);
