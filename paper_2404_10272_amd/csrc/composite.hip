@@ -33,6 +33,11 @@ template <int kCtrl>
 __device__ __forceinline__ float dpp(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));
 }
+// the lane whose place differs in the bits a permutation of four lanes exchanges
+template <int kCtrl>
+__device__ __forceinline__ int32_t lane_xor(int32_t x) {
+    return __builtin_amdgcn_update_dpp(0, x, kCtrl, 0xF, 0xF, true);
+}
 // inclusive prefix sum over the row (lane 15 ends with the row total)
 __device__ __forceinline__ float row_prefix(float x) {
     x += dpp<0x111>(x);
@@ -372,8 +377,8 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
 // the field's blobs are zero): nk = -log2(e) / (2 radius^2), so that
 // g = exp2(|x - c|^2 nk) is one hardware exp2; channels of a blob: 1, r, g, b.
 struct BlobArgs {
-    double cx[OGV_MAX_BLOBS], cy[OGV_MAX_BLOBS], cz[OGV_MAX_BLOBS], nk64[OGV_MAX_BLOBS];
-    float nk[OGV_MAX_BLOBS], a[OGV_MAX_BLOBS];
+    double nk64[OGV_MAX_BLOBS];
+    float cx[OGV_MAX_BLOBS], cy[OGV_MAX_BLOBS], cz[OGV_MAX_BLOBS], nk[OGV_MAX_BLOBS], a[OGV_MAX_BLOBS];
     float channel[OGV_MAX_BLOBS][4];
 };
 
@@ -420,24 +425,76 @@ struct Blobs {
     }
 };
 
+// The same from the sample's place, which needs nothing per ray and blob, but
+// seven more instructions per sample and blob.  A loop that loads each blob's
+// parameters to scalar registers as it comes to it: unrolled, they would take the
+// other form's registers and waves.
+template <int kN>
+__device__ __forceinline__ void add_at(const BlobArgs &f, float x, float y, float z, Acc &acc) {
+    constexpr int kUnroll = kN <= 4 ? kN : 2;
+#pragma unroll kUnroll
+    for (int k = 0; k < kN; ++k) {
+        const float ex = x - f.cx[k], ey = y - f.cy[k], ez = z - f.cz[k];
+        const float w = f.a[k] * __builtin_amdgcn_exp2f(fmaf(ex, ex, fmaf(ey, ey, ez * ez)) * f.nk[k]);
+        acc[0] += w;
+#pragma unroll
+        for (int q = 1; q < 4; ++q) acc[q] = fmaf(w, f.channel[k][q], acc[q]);
+    }
+}
+
+// Sums of a ray, or of its part in a row's range: the lane's own samples, and the
+// depth before the row's next ones.
+struct RaySums {
+    float r, g, b, opacity, depth;
+};
+// adds one sample a lane (sum: its sigma and sigma times colour; ok: it is one)
+__device__ __forceinline__ void composite_row(RaySums &q, const Acc &sum, float dt, bool ok) {
+    const float sig = sum[0];
+    // the hardware's reciprocal, refined; it gives 0 where that would be no normal number
+    float inv = __builtin_amdgcn_rcpf(sig);
+    inv = sig >= 0x1p-126f ? fmaf(fmaf(-sig, inv, 1.f), inv, inv) : 0.f;
+    if (__any(sig > 0x1p125f)) inv = sig > 0x1p125f ? 1.f / sig : inv;
+    const float tau = ok ? sig * dt : 0.f;
+    const float incl = row_prefix(tau);
+    const float wt = exp_neg(q.depth + dpp<0x111>(incl)) * alpha_of(tau);
+    const float wi = wt * inv;
+    q.r = fmaf(wi, sum[1], q.r);
+    q.g = fmaf(wi, sum[2], q.g);
+    q.b = fmaf(wi, sum[3], q.b);
+    q.opacity += wt;
+    q.depth += row_bcast<kRow - 1>(incl);
+}
+
 // A wave renders `per` consecutive rays (at most kWaveRays), whose samples are
-// cut into chunks of 16, one sample a lane of a row.  The chunks of the wave's
-// rays, in order, are dealt to its four rows in four contiguous ranges of equal
-// length: with a ray a row, rows would wait for the longest of four.  A ray cut
-// by a range's end is rendered in parts, each as if it began with
-// transmittance one, and the parts are put together at the end
-// (C = C_1 + T_1 (C_2 + T_2 ...), T_k = exp(-depth of part k)).
+// cut into chunks of 16, one sample a lane of a row, in one of two ways.
+//
+// A ray a row, four rays at a time: nothing is prepared, and a turn evaluates the
+// blobs at the samples' places (add_at).  Rows wait for the longest of four.
+//
+// Dealt: the chunks of the wave's rays, in order, go to its four rows in four
+// contiguous ranges of equal length, and the blobs are evaluated along the ray
+// (Blobs).  A ray cut by a range's end is rendered in parts, each as if it began
+// with transmittance one, and the parts are put together at the end
+// (C = C_1 + T_1 (C_2 + T_2 ...), T_k = exp(-depth of part k)).  A turn costs
+// less, but every wave pays for the rays' blobs and for the parts about as much
+// as for two turns of twelve blobs.
+//
+// So short rays, rays of like lengths and fields of few blobs take the first way.
+// 640,000 rays, the way taken (always dealt): 8 samples each and 1 blob 37 us
+// (84), 12 blobs 67 (106); 40 each, 12 blobs 155 (185); 800x800 rays of one
+// object, 1 blob 71 (109), 12 blobs 164 (174); random lengths of 40 on average
+// are dealt: 193, and 290 with a ray a row.
 //
 // Sigma and colour are computed in registers from the field at each sample's
-// midpoint.  The sums over blobs of the weight and of its three colour products
-// are a contraction of the blobs' channels with the sample's weights, one matrix
-// instruction (4x4x1, 16 blocks) a blob, which leaves each lane its own
-// sample's four sums and runs beside the vector ALU.  The loops are wave-uniform,
-// as matrix instructions ignore the lane mask.
+// midpoint.  Along the ray, the sums over blobs of the weight and of its three
+// colour products are a contraction of the blobs' channels with the sample's
+// weights, one matrix instruction (4x4x1, 16 blocks) a blob, which leaves each
+// lane its own sample's four sums and runs beside the vector ALU.  The loops are
+// wave-uniform, as matrix instructions ignore the lane mask.
 //
-// Bound by VALU issue, the exponentials' quarter rate first: 640,000 rays of 25.4 M
-// samples through 12 blobs take 191 us.  Twelve instructions a blob and sample
-// and a ray a row took 311 us; the form below with a ray a row 265.
+// Bound by VALU issue: 640,000 rays of 25.4 M samples through 12 blobs take 193 us,
+// of which the blobs' own instructions are about two fifths.  At the 64 registers
+// of eight waves a SIMD; at seven 200 us.
 constexpr int kWaveRays = 8;
 struct RenderLds {
     float2 uw[kWaveRays][kRow];        // u_k, W_k of each ray with samples
@@ -457,7 +514,7 @@ __device__ __forceinline__ void wave_fence() {
 }
 
 template <int kN>
-__global__ void __launch_bounds__(kBlock) render_blobs_kernel(const int64_t *__restrict__ offsets, int64_t n_rays,
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) render_blobs_kernel(const int64_t *__restrict__ offsets, int64_t n_rays,
                                                              int per, const float *__restrict__ origins,
                                                              const float *__restrict__ dirs,
                                                              const float *__restrict__ t0,
@@ -473,6 +530,54 @@ __global__ void __launch_bounds__(kBlock) render_blobs_kernel(const int64_t *__r
     const bool live = lane < per && r0 + lane < n_rays;
     const int64_t a = live ? offsets[r0 + lane] : 0, b = live ? offsets[r0 + lane + 1] : 0;
     const int32_t chunks = b > a ? (int32_t)((b - a + kRow - 1) / kRow) : 0;
+    // a ray a row where that costs less: a turn (16 samples a row) by either way
+    // and the dealing, in twelfths of a microsecond for every wave of 640,000
+    // rays, from equal lengths of 40 and 96 samples through 1 to 16 blobs
+    constexpr int kTurnAt = 100 + 17 * kN, kTurnAlong = 114 + 12 * kN, kDeal = 500;
+    int32_t most = max(chunks, lane_xor<0xb1>(chunks));   // of the ray's four
+    most = max(most, lane_xor<0x4e>(most));
+    int32_t all = chunks + lane_xor<0xb1>(chunks);
+    all += lane_xor<0x4e>(all);
+    const int32_t turns[2] = {__builtin_amdgcn_readlane(most, 0), __builtin_amdgcn_readlane(most, 4)};
+    const int32_t dealt = (__builtin_amdgcn_readlane(all, 0) + __builtin_amdgcn_readlane(all, 4) + 3) / 4;
+    if ((int64_t)(turns[0] + turns[1]) * kTurnAt <= (int64_t)dealt * kTurnAlong + kDeal) {
+        for (int h = 0; 4 * h < per; ++h) {
+            const int64_t r = r0 + 4 * h + row;
+            if (r0 + 4 * h >= n_rays) break;   // wave-uniform
+            const int64_t from = __shfl(a, 4 * h + row, 64), to = __shfl(b, 4 * h + row, 64);
+            float o[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 0.f};
+            if (to > from) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    o[k] = origins[3 * r + k];
+                    d[k] = dirs[3 * r + k];
+                }
+            }
+            RaySums q{};
+            int64_t g = from + l;
+            for (int32_t k = 0; k < turns[h]; ++k, g += kRow) {   // wave-uniform
+                const bool ok = g < to;
+                float m = 0.f, dt = 0.f;
+                if (ok) {
+                    const float t_a = t0[g], t_b = t1[g];
+                    m = 0.5f * (t_a + t_b);
+                    dt = t_b - t_a;
+                }
+                Acc sum = {0.f, 0.f, 0.f, 0.f};
+                add_at<kN>(f, fmaf(d[0], m, o[0]), fmaf(d[1], m, o[1]), fmaf(d[2], m, o[2]), sum);
+                composite_row(q, sum, dt, ok);
+            }
+            const float sr = row_prefix(q.r), sg = row_prefix(q.g), sb = row_prefix(q.b), sa = row_prefix(q.opacity);
+            if (l == kRow - 1 && r < n_rays) {
+                out_rgb[3 * r + 0] = sr;
+                out_rgb[3 * r + 1] = sg;
+                out_rgb[3 * r + 2] = sb;
+                if (out_opacity) out_opacity[r] = sa;
+            }
+        }
+        return;
+    }
+
     const uint64_t some = __ballot(chunks > 0);
     const int rays = __popcll(some), slot = __popcll(some & ((1ull << lane) - 1));
     int32_t last = chunks;   // inclusive scan over the first 16 lanes
@@ -504,8 +609,8 @@ __global__ void __launch_bounds__(kBlock) render_blobs_kernel(const int64_t *__r
         double tc = 0., len = 0.;
         if (ok) {
             const int64_t r = r0 + w.ray[i];
-            const double ex = origins[3 * r] - f.cx[l], ey = origins[3 * r + 1] - f.cy[l];
-            const double ez = origins[3 * r + 2] - f.cz[l];
+            const double ex = (double)origins[3 * r] - f.cx[l], ey = (double)origins[3 * r + 1] - f.cy[l];
+            const double ez = (double)origins[3 * r + 2] - f.cz[l];
             const double dx = dirs[3 * r], dy = dirs[3 * r + 1], dz = dirs[3 * r + 2];
             len = w.len[i];
             tc = -fma(dx, ex, fma(dy, ey, dz * ez)) * w.inv_dd[i];
@@ -537,7 +642,7 @@ __global__ void __launch_bounds__(kBlock) render_blobs_kernel(const int64_t *__r
     int32_t next = c;        // first chunk past it
     int64_t g = 0, to = 0;   // first sample of the current chunk, end of the ray's samples
     float u = 0.f, W = 0.f, ref = 0.f, scale = 0.f;
-    float cr = 0.f, cg = 0.f, cb = 0.f, acc = 0.f, depth = 0.f;
+    RaySums q{};
     while (__any(c < end)) {
         if (c < end && c == next) {   // row-uniform: on to the next ray
             if (i < 0) {
@@ -555,7 +660,7 @@ __global__ void __launch_bounds__(kBlock) render_blobs_kernel(const int64_t *__r
             next = w.start[i + 1];
             to = w.to[i];
             g = w.from[i] + (int64_t)(c - w.start[i]) * kRow;
-            cr = cg = cb = acc = depth = 0.f;
+            q = RaySums{};
         }
         const bool ok = c < end && g + l < to;
         float s = 0.f, dt = 0.f;
@@ -566,28 +671,15 @@ __global__ void __launch_bounds__(kBlock) render_blobs_kernel(const int64_t *__r
         }
         Acc sum = {0.f, 0.f, 0.f, 0.f};
         Blobs<0, kN>::add(f, channel, s, u, W, sum);
-        const float sig = sum[0];
-        // the hardware's reciprocal, refined; it gives 0 where that would be no normal number
-        float inv = __builtin_amdgcn_rcpf(sig);
-        inv = sig >= 0x1p-126f ? fmaf(fmaf(-sig, inv, 1.f), inv, inv) : 0.f;
-        if (__any(sig > 0x1p125f)) inv = sig > 0x1p125f ? 1.f / sig : inv;
-        const float tau = ok ? sig * dt : 0.f;
-        const float incl = row_prefix(tau);
-        const float wt = exp_neg(depth + dpp<0x111>(incl)) * alpha_of(tau);
-        const float wi = wt * inv;
-        cr = fmaf(wi, sum[1], cr);
-        cg = fmaf(wi, sum[2], cg);
-        cb = fmaf(wi, sum[3], cb);
-        acc += wt;
-        depth += row_bcast<kRow - 1>(incl);
+        composite_row(q, sum, dt, ok);
         const bool mine = c < end;
         ++c;
         g += kRow;
         if (mine && (c == next || c == end)) {   // row-uniform: the ray, or its part here, ends
-            const float sr = row_prefix(cr), sg = row_prefix(cg), sb = row_prefix(cb), sa = row_prefix(acc);
+            const float sr = row_prefix(q.r), sg = row_prefix(q.g), sb = row_prefix(q.b), sa = row_prefix(q.opacity);
             if (l == kRow - 1) {
                 float *p = w.part[i][row];
-                p[0] = depth;
+                p[0] = q.depth;
                 p[1] = sr;
                 p[2] = sg;
                 p[3] = sb;
@@ -682,9 +774,9 @@ extern "C" ogv_status ogv_render_blobs(const int64_t *offsets, int64_t n_rays, c
     if (n_rays == 0) return OGV_OK;
     if (!offsets || !origins || !dirs || !t0 || !t1 || !out_rgb) OGV_FAIL(OGV_ERR_INVALID, "null argument");
     hipStream_t s = (hipStream_t)stream;
-    // 8 rays a wave even their lengths out (640,000 rays of random lengths 191 us
-    // against 215 with 4) and still part the long rays of an image's middle
-    // (800x800 rays of one object 170 us, with 4 rays 175; 16 take 187 on the
+    // 8 rays a wave even their lengths out (640,000 rays of random lengths, all
+    // dealt, 191 us against 215 with 4) and still part the long rays of an image's
+    // middle (800x800 rays of one object 170 us, with 4 rays 175; 16 take 187 on the
     // random lengths and 190 here).  Calls of fewer rays need the waves instead:
     // half that image 96 us with 4 against 101 with 8, a quarter 57 against 68,
     // 300,000 random rays 108 against 99
