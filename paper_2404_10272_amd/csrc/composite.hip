@@ -142,13 +142,14 @@ __device__ __forceinline__ void load_group(int64_t i, int64_t b, int64_t total, 
 }
 
 // exp(-x), by the hardware's base-2 exponential of a product kept to twice
-// the precision of a float (x up to a few hundred otherwise loses bits there)
+// the precision of a float (x up to a few hundred otherwise loses bits there);
+// beyond the range of the result the power alone, 0 or infinity (or NaN)
 __device__ __forceinline__ float exp_neg(float x) {
     constexpr float L = 1.44269502f, l = 1.92596303e-8f;   // log2(e) = L + l
     const float y = -x * L;
     const float e = fmaf(-x, L, -y) - x * l;
     const float p = __builtin_amdgcn_exp2f(y);
-    return __builtin_isfinite(y) ? fmaf(p, e * 0.693147181f, p) : p;
+    return fabsf(y) < 128.f ? fmaf(p, e * 0.693147181f, p) : p;
 }
 
 // alpha = 1 - exp(-tau).  Up to an optical depth of one it is
@@ -186,6 +187,10 @@ __device__ __forceinline__ void alphas(const float tau[kPer], float alpha[kPer])
     }
 }
 
+// T alpha; 0 for an opacity of 0, as past a ray's end, whatever the transmittance
+// (with negative densities it may be infinite)
+__device__ __forceinline__ float weight(float T, float alpha) { return alpha == 0.f ? 0.f : T * alpha; }
+
 // One 16-lane row per ray.  The optical depth before a lane's samples is a
 // row prefix sum of the lanes' depths plus the carry of earlier chunks; every
 // sample's transmittance is an exponential of its own (multiplying one on
@@ -218,7 +223,7 @@ __global__ void __launch_bounds__(kBlock) composite_fwd_kernel(const int64_t *__
         float depth = carry + dpp<0x111>(incl);
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            const float w = exp_neg(depth) * alpha[k];
+            const float w = weight(exp_neg(depth), alpha[k]);
             cr = fmaf(w, c[3 * k], cr);
             cg = fmaf(w, c[3 * k + 1], cg);
             cb = fmaf(w, c[3 * k + 2], cb);
@@ -327,7 +332,7 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
             float wq = 0.f;
 #pragma unroll
             for (int k = 0; k < kPer; ++k) {
-                w[k] = T * alpha[k];
+                w[k] = weight(T, alpha[k]);
                 d += tau[h][k];
                 next[k] = T = exp_neg(d);
                 wq = fmaf(w[k], q[h][k], wq);
