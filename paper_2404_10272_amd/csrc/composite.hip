@@ -69,6 +69,12 @@ __device__ __forceinline__ float row_min(float x) {
     return row_bcast<kRow - 1>(dpp_min<0x118>(dpp_min<0x114>(dpp_min<0x112>(dpp_min<0x111>(x)))));
 }
 
+// value of lane kLane (0..3) of this lane's four
+template <int kLane>
+__device__ __forceinline__ float quad_bcast(float x) {
+    return dpp<kLane * 0x55>(x);
+}
+
 // Each lane takes kPer consecutive samples of its row's ray, so a row covers
 // kChunk samples per pass and reads them with 16-byte loads (three for t0, t1
 // and sigma, three for the colours), where one sample a lane took six 4-byte
@@ -141,6 +147,23 @@ __device__ __forceinline__ void load_group(int64_t i, int64_t b, int64_t total, 
     }
 }
 
+// One sample of a ray ending at b (zero past it).
+struct Sample {
+    float dt, tau, c[3];
+};
+__device__ __forceinline__ Sample load_one(int64_t i, int64_t b, const float *__restrict__ t0,
+                                           const float *__restrict__ t1, const float *__restrict__ sigma,
+                                           const float *__restrict__ rgb) {
+    Sample x{};
+    if (i < b) {
+        x.dt = t1[i] - t0[i];
+        x.tau = sigma[i] * x.dt;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x.c[q] = rgb[3 * i + q];
+    }
+    return x;
+}
+
 // exp(-x), by the hardware's base-2 exponential of a product kept to twice
 // the precision of a float (x up to a few hundred otherwise loses bits there);
 // beyond the range of the result the power alone, 0 or infinity (or NaN)
@@ -191,6 +214,58 @@ __device__ __forceinline__ void alphas(const float tau[kPer], float alpha[kPer])
 // (with negative densities it may be infinite)
 __device__ __forceinline__ float weight(float T, float alpha) { return alpha == 0.f ? 0.f : T * alpha; }
 
+// Four samples a lane cost four samples' arithmetic however few a ray has, so a
+// wave none of whose rays has more than 16 takes one sample a lane: 640,000 rays
+// of 8 samples each 35 us forward and 60 backward, against 54 and 83.  A ray's
+// result does not depend on the rays that share its wave: four lanes then do the
+// sums of the one lane, in its order, and the steps that only add zeros are left
+// out.  (To choose for each ray by its own length, and add in any order, makes
+// waves of long and short rays run both forms: 139 us where 130 were, over
+// 640,000 rays of 40 samples on average.  Two samples a lane, for rays of up to 32,
+// measured no better than four.)
+//
+// Optical depth before a lane's sample, and (all, in the last lane) of the ray:
+// the quads' sums first, their prefix, then the quad's samples one by one.
+__device__ __forceinline__ float depth_of_one(float tau, float &all) {
+    const int k = threadIdx.x & 3;
+    float s = tau + dpp<0xb1>(tau);   // of two, then of four lanes
+    s += dpp<0x4e>(s);
+    s += dpp<0x114>(s);
+    s += dpp<0x118>(s);
+    all = s;
+    float d = dpp<0x114>(s);
+    // read by all lanes, before any of them is left out
+    const float tau0 = quad_bcast<0>(tau), tau1 = quad_bcast<1>(tau), tau2 = quad_bcast<2>(tau);
+    d += k > 0 ? tau0 : 0.f;
+    d += k > 1 ? tau1 : 0.f;
+    d += k > 2 ? tau2 : 0.f;
+    return d;
+}
+// sum of w c over a quad's lanes, one after the other (in its last lane)
+__device__ __forceinline__ float quad_chain(float w, float c) {
+    float x = fmaf(w, c, 0.f);
+#pragma unroll
+    for (int step = 1; step < kPer; ++step) {
+        const float y = fmaf(w, c, dpp<0x111>(x));
+        x = (threadIdx.x & 3) == step ? y : x;
+    }
+    return x;
+}
+// sum over the row's quads of their last lane's value (in the row's last lane)
+__device__ __forceinline__ float quads_total(float x) {
+    x += dpp<0x114>(x);
+    x += dpp<0x118>(x);
+    return x;
+}
+
+__device__ __forceinline__ void write_pixel(float *out_rgb, float *out_opacity, int64_t r, float cr, float cg, float cb,
+                                            float acc) {
+    out_rgb[3 * r + 0] = cr;
+    out_rgb[3 * r + 1] = cg;
+    out_rgb[3 * r + 2] = cb;
+    if (out_opacity) out_opacity[r] = acc;
+}
+
 // One 16-lane row per ray.  The optical depth before a lane's samples is a
 // row prefix sum of the lanes' depths plus the carry of earlier chunks; every
 // sample's transmittance is an exponential of its own (multiplying one on
@@ -215,6 +290,17 @@ __global__ void __launch_bounds__(kBlock) composite_fwd_kernel(const int64_t *__
     const bool live = r < n_rays;
     const int64_t a = live ? offsets[r] : 0, b = live ? offsets[r + 1] : 0, total = offsets[n_rays];
     float cr = 0.f, cg = 0.f, cb = 0.f, acc = 0.f, carry = 0.f;
+    if (!__any(b - a > kRow)) {   // wave-uniform: one sample a lane
+        const Sample x = load_one(a + l, b, t0, t1, sigma, rgb);
+        float all;
+        const float w = weight(exp_neg(depth_of_one(x.tau, all)), alpha_of(x.tau));
+        cr = quads_total(quad_chain(w, x.c[0]));
+        cg = quads_total(quad_chain(w, x.c[1]));
+        cb = quads_total(quad_chain(w, x.c[2]));
+        acc = quads_total(quad_chain(w, 1.f));
+        if (live && l == kRow - 1) write_pixel(out_rgb, out_opacity, r, cr, cg, cb, acc);
+        return;
+    }
     for (int64_t g0 = a; g0 < b; g0 += kChunk) {   // row-uniform
         float dt[kPer], tau[kPer], c[3 * kPer], alpha[kPer];
         load_group<true>(g0 + kPer * l, b, total, t0, t1, sigma, rgb, dt, tau, c);
@@ -236,11 +322,20 @@ __global__ void __launch_bounds__(kBlock) composite_fwd_kernel(const int64_t *__
     cg = row_prefix(cg);
     cb = row_prefix(cb);
     acc = row_prefix(acc);
-    if (live && l == kRow - 1) {
-        out_rgb[3 * r + 0] = cr;
-        out_rgb[3 * r + 1] = cg;
-        out_rgb[3 * r + 2] = cb;
-        if (out_opacity) out_opacity[r] = acc;
+    if (live && l == kRow - 1) write_pixel(out_rgb, out_opacity, r, cr, cg, cb, acc);
+}
+
+// Samples no ray owns (before offsets[0] = lo, from offsets[n_rays] = hi on) get
+// zero gradient; the launch's threads share them.
+__device__ __forceinline__ void zero_unowned(int64_t lo, int64_t hi, int64_t n_samples, float *__restrict__ d_sigma,
+                                             float *__restrict__ d_rgb) {
+    const int64_t before = lo < n_samples ? lo : n_samples, after = hi < n_samples ? n_samples - hi : 0;
+    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < before + after; k += (int64_t)gridDim.x * kBlock) {
+        const int64_t i = k < before ? k : hi + (k - before);
+        d_sigma[i] = 0.f;
+        d_rgb[3 * i + 0] = 0.f;
+        d_rgb[3 * i + 1] = 0.f;
+        d_rgb[3 * i + 2] = 0.f;
     }
 }
 
@@ -281,6 +376,32 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
     // first sample of the last span (the ray's spans start at a)
     const int64_t last = b > a ? a + ((b - a - 1) / kSpan) * kSpan : a;
 
+    if (!__any(b - a > kRow)) {   // wave-uniform: one sample a lane, as in the forward pass
+        const int64_t i = a + l;
+        const Sample x = load_one(i, b, t0, t1, sigma, rgb);
+        const float q = (float)fma(db, (double)x.c[2], fma(dg, (double)x.c[1], dr * (double)x.c[0]));
+        float all;
+        const float d = depth_of_one(x.tau, all), w = weight(exp_neg(d), alpha_of(x.tau)), next = exp_neg(d + x.tau);
+        const float end = ga * expf(-row_bcast<kRow - 1>(all));
+        // sum over the later quads, then over the quad's later lanes, one after the other
+        float qs = quad_bcast<kPer - 1>(quad_chain(w, q));
+        qs += dpp<0x104>(qs);
+        qs += dpp<0x108>(qs);
+        float S = dpp<0x104>(qs);
+#pragma unroll
+        for (int step = kPer - 2; step >= 0; --step) {
+            const float later = fmaf(dpp<0x101>(w), dpp<0x101>(q), dpp<0x101>(S));
+            S = (threadIdx.x & 3) == step ? later : S;
+        }
+        if (i < b) {
+            d_sigma[i] = x.dt * (fmaf(next, q, -S) + end);
+            d_rgb[3 * i + 0] = w * gr;
+            d_rgb[3 * i + 1] = w * gg;
+            d_rgb[3 * i + 2] = w * gb;
+        }
+        zero_unowned(offsets[0], hi, n_samples, d_sigma, d_rgb);
+        return;
+    }
     float dt[kKeep][kPer], tau[kKeep][kPer], q[kKeep][kPer];
     const auto load_span = [&](int64_t g0) {
 #pragma unroll
@@ -364,16 +485,7 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
         }
         if (g0 == a) break;
     }
-    // samples no ray owns (before offsets[0], from offsets[n_rays] on) get zero gradient
-    const int64_t lo = offsets[0];
-    const int64_t before = lo < n_samples ? lo : n_samples, after = hi < n_samples ? n_samples - hi : 0;
-    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < before + after; k += (int64_t)gridDim.x * kBlock) {
-        const int64_t i = k < before ? k : hi + (k - before);
-        d_sigma[i] = 0.f;
-        d_rgb[3 * i + 0] = 0.f;
-        d_rgb[3 * i + 1] = 0.f;
-        d_rgb[3 * i + 2] = 0.f;
-    }
+    zero_unowned(offsets[0], hi, n_samples, d_sigma, d_rgb);
 }
 
 // ------------------------------------------------------------------ blob field
