@@ -95,26 +95,29 @@ __device__ __forceinline__ void store4(float *p, float a, float b, float c, floa
     *reinterpret_cast<Quad *>(p) = Quad{{a, b, c, d}};
 }
 
-// Step lengths and optical depths of samples i .. i+3 of a ray ending at b
-// (zero past it), and their colours when rgb is given.  A group may run past
-// the ray into the next one's samples, whose values are dropped; only past
-// `total`, the end of all rays' samples, is nothing read.
-template <bool kColour>
+// Step lengths and optical depths (kDepths) of samples i .. i+3 of a ray ending at
+// b, and their colours (kColours); zero past it.  A group may run past the ray into
+// the next one's samples, whose values are dropped; only past `total`, the end of
+// all rays' samples, is nothing read.
+template <bool kDepths, bool kColours>
 __device__ __forceinline__ void load_group(int64_t i, int64_t b, int64_t total, const float *__restrict__ t0,
                                            const float *__restrict__ t1, const float *__restrict__ sigma,
                                            const float *__restrict__ rgb, float dt[kPer], float tau[kPer],
                                            float c[3 * kPer]) {
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) dt[k] = tau[k] = 0.f;
-#pragma unroll
-    for (int k = 0; k < 3 * kPer; ++k) c[k] = 0.f;
+    for (int k = 0; k < kPer; ++k) {
+        if (kDepths) dt[k] = tau[k] = 0.f;
+        if (kColours) c[3 * k] = c[3 * k + 1] = c[3 * k + 2] = 0.f;
+    }
     if (i >= b) return;
     float u[kPer], v[kPer], s[kPer];
     if (i + kPer <= total) {
-        load4(t0 + i, u);
-        load4(t1 + i, v);
-        load4(sigma + i, s);
-        if (kColour) {
+        if (kDepths) {
+            load4(t0 + i, u);
+            load4(t1 + i, v);
+            load4(sigma + i, s);
+        }
+        if (kColours) {
             load4(rgb + 3 * i, c);
             load4(rgb + 3 * i + 4, c + 4);
             load4(rgb + 3 * i + 8, c + 8);
@@ -124,10 +127,12 @@ __device__ __forceinline__ void load_group(int64_t i, int64_t b, int64_t total, 
         for (int k = 0; k < kPer; ++k) {
             u[k] = v[k] = s[k] = 0.f;
             if (i + k < b) {
-                u[k] = t0[i + k];
-                v[k] = t1[i + k];
-                s[k] = sigma[i + k];
-                if (kColour) {
+                if (kDepths) {
+                    u[k] = t0[i + k];
+                    v[k] = t1[i + k];
+                    s[k] = sigma[i + k];
+                }
+                if (kColours) {
                     c[3 * k] = rgb[3 * (i + k)];
                     c[3 * k + 1] = rgb[3 * (i + k) + 1];
                     c[3 * k + 2] = rgb[3 * (i + k) + 2];
@@ -138,9 +143,11 @@ __device__ __forceinline__ void load_group(int64_t i, int64_t b, int64_t total, 
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
         const bool ok = i + k < b;
-        dt[k] = ok ? v[k] - u[k] : 0.f;
-        tau[k] = ok ? s[k] * dt[k] : 0.f;
-        if (kColour) {
+        if (kDepths) {
+            dt[k] = ok ? v[k] - u[k] : 0.f;
+            tau[k] = ok ? s[k] * dt[k] : 0.f;
+        }
+        if (kColours) {
 #pragma unroll
             for (int q = 0; q < 3; ++q) c[3 * k + q] = ok ? c[3 * k + q] : 0.f;
         }
@@ -303,7 +310,7 @@ __global__ void __launch_bounds__(kBlock) composite_fwd_kernel(const int64_t *__
     }
     for (int64_t g0 = a; g0 < b; g0 += kChunk) {   // row-uniform
         float dt[kPer], tau[kPer], c[3 * kPer], alpha[kPer];
-        load_group<true>(g0 + kPer * l, b, total, t0, t1, sigma, rgb, dt, tau, c);
+        load_group<true, true>(g0 + kPer * l, b, total, t0, t1, sigma, rgb, dt, tau, c);
         alphas(tau, alpha);
         const float incl = row_prefix((tau[0] + tau[1]) + (tau[2] + tau[3]));
         float depth = carry + dpp<0x111>(incl);
@@ -339,13 +346,12 @@ __device__ __forceinline__ void zero_unowned(int64_t lo, int64_t hi, int64_t n_s
     }
 }
 
-// One 16-lane row per ray, in spans of kKeep chunks.  Pass 1: the optical
-// depth before the ray's last span, which stays in registers.  Pass 2, spans
-// from the back: T_i from the depth before it (the span's, less a span at each
-// step back, plus row prefix sums), and S_i = sum_{k>i} w_k q_k by a row
-// suffix sum plus the carry -- never as C minus a prefix.  The upstream
-// gradient is constant along a ray, so a sample's colour enters only as
-// q_i = g_C . c_i:
+// One 16-lane row per ray.  Pass 1: the optical depth before the ray's last chunk,
+// which stays in registers, as do the depths of the chunk before it.  Pass 2,
+// chunks from the back: T_i from the depth before the chunk (at each step back less
+// the chunk's) plus row prefix sums, and S_i = sum_{k>i} w_k q_k by a row suffix
+// sum plus the carry -- never as C minus a prefix.  The upstream gradient is
+// constant along a ray, so a sample's colour enters only as q_i = g_C . c_i:
 //   dL/dsigma_i = dt_i (T_{i+1} q_i - S_i + g_A T_n).
 // One suffix sum instead of three, and one register a sample instead of three;
 // the products of q are summed in 64 bits, as they may cancel.  T_n is the
@@ -354,11 +360,10 @@ __device__ __forceinline__ void zero_unowned(int64_t lo, int64_t hi, int64_t n_s
 // a small difference of numbers near one on every opaque ray.
 //
 // Bound by HBM: 640,000 rays with 25.4 M samples, 614 MB in and 407 MB out,
-// take 263 us, 3.9 TB/s; one sample a lane took 375 us.  kKeep = 1: with two
-// chunks a span 270 us (170 against 164 at 24 samples a ray, 65 against 54 at
-// 8, 287 against 292 at 96), with three 302 and with four 351, as more
+// take 255 us, 4.0 TB/s; one sample a lane took 375 us.  The depths kept from
+// pass 1 took 5 to 10% off rays of more than 64 samples (640,000 of 100 each 565 us
+// against 616).  Two chunks kept whole took 270 us, three 302 and four 351, as more
 // registers leave fewer waves.
-constexpr int kKeep = 1;
 __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
     const int64_t *__restrict__ offsets, int64_t n_rays, int64_t n_samples, const float *__restrict__ t0,
     const float *__restrict__ t1,
@@ -372,10 +377,6 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
     const float gb = live ? g_rgb[3 * r + 2] : 0.f;
     const double dr = gr, dg = gg, db = gb;
     const float ga = live && g_opacity ? g_opacity[r] : 0.f;
-    constexpr int kSpan = kKeep * kChunk;
-    // first sample of the last span (the ray's spans start at a)
-    const int64_t last = b > a ? a + ((b - a - 1) / kSpan) * kSpan : a;
-
     if (!__any(b - a > kRow)) {   // wave-uniform: one sample a lane, as in the forward pass
         const int64_t i = a + l;
         const Sample x = load_one(i, b, t0, t1, sigma, rgb);
@@ -402,87 +403,73 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
         zero_unowned(offsets[0], hi, n_samples, d_sigma, d_rgb);
         return;
     }
-    float dt[kKeep][kPer], tau[kKeep][kPer], q[kKeep][kPer];
-    const auto load_span = [&](int64_t g0) {
-#pragma unroll
-        for (int h = 0; h < kKeep; ++h) {
-            float c[3 * kPer];
-            load_group<true>(g0 + h * kChunk + kPer * l, b, hi, t0, t1, sigma, rgb, dt[h], tau[h], c);
-#pragma unroll
-            for (int k = 0; k < kPer; ++k) 
-                q[h][k] = (float)fma(db, (double)c[3 * k + 2], fma(dg, (double)c[3 * k + 1], dr * (double)c[3 * k]));
-        }
-    };
+    const int64_t last = b > a ? a + (b - a - 1) / kChunk * kChunk : a;   // first sample of the last chunk
+    float dt[kPer], tau[kPer], q[kPer], c[3 * kPer];
+    float dt_before[kPer] = {}, tau_before[kPer] = {};   // of the chunk before it
     float part = 0.f;
-    for (int64_t g0 = a; g0 < last; g0 += kChunk) {   // the spans before the last
-        float u[kPer], v[kPer], none[3 * kPer];
-        load_group<false>(g0 + kPer * l, b, hi, t0, t1, sigma, rgb, u, v, none);
-        part += (v[0] + v[1]) + (v[2] + v[3]);
+    for (int64_t g0 = a; g0 < last; g0 += kChunk) {   // the chunks before the last
+        load_group<true, false>(g0 + kPer * l, b, hi, t0, t1, sigma, rgb, dt_before, tau_before, c);
+        part += (tau_before[0] + tau_before[1]) + (tau_before[2] + tau_before[3]);
     }
-    load_span(last);
-    float depth = row_bcast<kRow - 1>(row_prefix(part));   // before the span
+    load_group<true, true>(last + kPer * l, b, hi, t0, t1, sigma, rgb, dt, tau, c);
+    float depth = row_bcast<kRow - 1>(row_prefix(part));   // before the chunk
     float later = 0.f;                                     // sum of w q over the later chunks
     float end = 0.f;                                       // g_A T_n
-    for (int64_t g0 = last; g0 >= a; g0 -= kSpan) {   // row-uniform
-        if (g0 != last) load_span(g0);
-        float before[kKeep], all[kKeep];   // depth before the lane in its chunk, of the chunk
-#pragma unroll
-        for (int h = 0; h < kKeep; ++h) {
-            const float incl = row_prefix((tau[h][0] + tau[h][1]) + (tau[h][2] + tau[h][3]));
-            before[h] = dpp<0x111>(incl);
-            all[h] = row_bcast<kRow - 1>(incl);
-        }
-        if (g0 != last) {
-#pragma unroll
-            for (int h = 0; h < kKeep; ++h) depth -= all[h];
-        }
-        if (g0 == a) depth = 0.f;
-        float at[kKeep];
-        at[0] = depth;
-#pragma unroll
-        for (int h = 1; h < kKeep; ++h) at[h] = at[h - 1] + all[h - 1];
-        if (g0 == last) end = ga * expf(-(at[kKeep - 1] + all[kKeep - 1]));
-#pragma unroll
-        for (int h = kKeep - 1; h >= 0; --h) {
-            if (g0 + h * kChunk >= b) continue;   // row-uniform
-            const int64_t i = g0 + h * kChunk + kPer * l;
-            float alpha[kPer], w[kPer], next[kPer];   // next: T_{i+1}
-            alphas(tau[h], alpha);
-            float d = at[h] + before[h];
-            float T = exp_neg(d);
-            float wq = 0.f;
+    for (int64_t g0 = last; g0 >= a; g0 -= kChunk) {   // row-uniform
+        const int64_t i = g0 + kPer * l;
+        if (g0 == last - kChunk) {
+            load_group<false, true>(i, b, hi, t0, t1, sigma, rgb, dt, tau, c);
 #pragma unroll
             for (int k = 0; k < kPer; ++k) {
-                w[k] = weight(T, alpha[k]);
-                d += tau[h][k];
-                next[k] = T = exp_neg(d);
-                wq = fmaf(w[k], q[h][k], wq);
+                dt[k] = dt_before[k];
+                tau[k] = tau_before[k];
             }
-            const float qs = row_suffix(wq);
-            float S = dpp<0x101>(qs) + later;   // sum over the samples of later lanes and chunks
-            float ds[kPer];
-#pragma unroll
-            for (int k = kPer - 1; k >= 0; --k) {
-                ds[k] = dt[h][k] * (fmaf(next[k], q[h][k], -S) + end);
-                S = fmaf(w[k], q[h][k], S);
-            }
-            if (i + kPer <= b) {
-                store4(d_sigma + i, ds[0], ds[1], ds[2], ds[3]);
-                store4(d_rgb + 3 * i, w[0] * gr, w[0] * gg, w[0] * gb, w[1] * gr);
-                store4(d_rgb + 3 * i + 4, w[1] * gg, w[1] * gb, w[2] * gr, w[2] * gg);
-                store4(d_rgb + 3 * i + 8, w[2] * gb, w[3] * gr, w[3] * gg, w[3] * gb);
-            } else {
-#pragma unroll
-                for (int k = 0; k < kPer; ++k)
-                    if (i + k < b) {
-                        d_sigma[i + k] = ds[k];
-                        d_rgb[3 * (i + k) + 0] = w[k] * gr;
-                        d_rgb[3 * (i + k) + 1] = w[k] * gg;
-                        d_rgb[3 * (i + k) + 2] = w[k] * gb;
-                    }
-            }
-            later += row_bcast<0>(qs);
+        } else if (g0 != last) {
+            load_group<true, true>(i, b, hi, t0, t1, sigma, rgb, dt, tau, c);
         }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            q[k] = (float)fma(db, (double)c[3 * k + 2], fma(dg, (double)c[3 * k + 1], dr * (double)c[3 * k]));
+        const float incl = row_prefix((tau[0] + tau[1]) + (tau[2] + tau[3])), all = row_bcast<kRow - 1>(incl);
+        if (g0 != last) depth -= all;
+        if (g0 == a) depth = 0.f;
+        if (g0 == last) end = ga * expf(-(depth + all));
+        float alpha[kPer], w[kPer], next[kPer];   // next: T_{i+1}
+        alphas(tau, alpha);
+        float d = depth + dpp<0x111>(incl);
+        float T = exp_neg(d);
+        float wq = 0.f;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            w[k] = weight(T, alpha[k]);
+            d += tau[k];
+            next[k] = T = exp_neg(d);
+            wq = fmaf(w[k], q[k], wq);
+        }
+        const float qs = row_suffix(wq);
+        float S = dpp<0x101>(qs) + later;   // sum over the samples of later lanes and chunks
+        float ds[kPer];
+#pragma unroll
+        for (int k = kPer - 1; k >= 0; --k) {
+            ds[k] = dt[k] * (fmaf(next[k], q[k], -S) + end);
+            S = fmaf(w[k], q[k], S);
+        }
+        if (i + kPer <= b) {
+            store4(d_sigma + i, ds[0], ds[1], ds[2], ds[3]);
+            store4(d_rgb + 3 * i, w[0] * gr, w[0] * gg, w[0] * gb, w[1] * gr);
+            store4(d_rgb + 3 * i + 4, w[1] * gg, w[1] * gb, w[2] * gr, w[2] * gg);
+            store4(d_rgb + 3 * i + 8, w[2] * gb, w[3] * gr, w[3] * gg, w[3] * gb);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kPer; ++k)
+                if (i + k < b) {
+                    d_sigma[i + k] = ds[k];
+                    d_rgb[3 * (i + k) + 0] = w[k] * gr;
+                    d_rgb[3 * (i + k) + 1] = w[k] * gg;
+                    d_rgb[3 * (i + k) + 2] = w[k] * gb;
+                }
+        }
+        later += row_bcast<0>(qs);
         if (g0 == a) break;
     }
     zero_unowned(offsets[0], hi, n_samples, d_sigma, d_rgb);
