@@ -8,8 +8,8 @@
 //   dL/dc_i     = w_i g_C
 //   dL/dsigma_i = dt_i (g_C . (T_{i+1} c_i - sum_{k>i} w_k c_k) + g_A T_n),
 // with the suffix sum accumulated in a reverse pass (not as C minus a
-// prefix) and T rebuilt from the exponent sum, whose absolute error stays
-// at the level of one rounding of the ray's total optical depth.  One 16-lane
+// prefix) and T from the optical depth before the sample: that before its
+// chunk of 64, kept in 64 bits, and float sums within the chunk.  One 16-lane
 // row (a DPP row) handles one ray, four consecutive samples a lane.
 #include <hip/hip_runtime.h>
 
@@ -69,6 +69,21 @@ __device__ __forceinline__ float row_min(float x) {
     return row_bcast<kRow - 1>(dpp_min<0x118>(dpp_min<0x114>(dpp_min<0x112>(dpp_min<0x111>(x)))));
 }
 
+// sum over the row in 64 bits, in every lane
+template <int kCtrl>
+__device__ __forceinline__ double dpp64(double x) {
+    const int64_t b = __double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, kCtrl, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), kCtrl, 0xF, 0xF, true);
+    return __longlong_as_double((int64_t)((uint64_t)hi << 32 | lo));
+}
+__device__ __forceinline__ double row_sum64(double x) {
+    x += dpp64<0x111>(x);
+    x += dpp64<0x112>(x);
+    x += dpp64<0x114>(x);
+    x += dpp64<0x118>(x);
+    return dpp64<0x150 + kRow - 1>(x);
+}
 // value of lane kLane (0..3) of this lane's four
 template <int kLane>
 __device__ __forceinline__ float quad_bcast(float x) {
@@ -349,7 +364,8 @@ __device__ __forceinline__ void zero_unowned(int64_t lo, int64_t hi, int64_t n_s
 // One 16-lane row per ray.  Pass 1: the optical depth before the ray's last chunk,
 // which stays in registers, as do the depths of the chunk before it.  Pass 2,
 // chunks from the back: T_i from the depth before the chunk (at each step back less
-// the chunk's) plus row prefix sums, and S_i = sum_{k>i} w_k q_k by a row suffix
+// the chunk's, both in 64 bits, so that a thick chunk leaves no rounding in those
+// before it) plus row prefix sums, and S_i = sum_{k>i} w_k q_k by a row suffix
 // sum plus the carry -- never as C minus a prefix.  The upstream gradient is
 // constant along a ray, so a sample's colour enters only as q_i = g_C . c_i:
 //   dL/dsigma_i = dt_i (T_{i+1} q_i - S_i + g_A T_n).
@@ -406,13 +422,14 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
     const int64_t last = b > a ? a + (b - a - 1) / kChunk * kChunk : a;   // first sample of the last chunk
     float dt[kPer], tau[kPer], q[kPer], c[3 * kPer];
     float dt_before[kPer] = {}, tau_before[kPer] = {};   // of the chunk before it
-    float part = 0.f;
+    const auto sum64 = [](const float v[kPer]) { return ((double)v[0] + v[1]) + ((double)v[2] + v[3]); };
+    double part = 0.;
     for (int64_t g0 = a; g0 < last; g0 += kChunk) {   // the chunks before the last
         load_group<true, false>(g0 + kPer * l, b, hi, t0, t1, sigma, rgb, dt_before, tau_before, c);
-        part += (tau_before[0] + tau_before[1]) + (tau_before[2] + tau_before[3]);
+        part += sum64(tau_before);
     }
     load_group<true, true>(last + kPer * l, b, hi, t0, t1, sigma, rgb, dt, tau, c);
-    float depth = row_bcast<kRow - 1>(row_prefix(part));   // before the chunk
+    double depth = row_sum64(part);   // before the chunk
     float later = 0.f;                                     // sum of w q over the later chunks
     float end = 0.f;                                       // g_A T_n
     for (int64_t g0 = last; g0 >= a; g0 -= kChunk) {   // row-uniform
@@ -431,12 +448,12 @@ __global__ void __launch_bounds__(kBlock) composite_bwd_kernel(
         for (int k = 0; k < kPer; ++k)
             q[k] = (float)fma(db, (double)c[3 * k + 2], fma(dg, (double)c[3 * k + 1], dr * (double)c[3 * k]));
         const float incl = row_prefix((tau[0] + tau[1]) + (tau[2] + tau[3])), all = row_bcast<kRow - 1>(incl);
-        if (g0 != last) depth -= all;
-        if (g0 == a) depth = 0.f;
-        if (g0 == last) end = ga * expf(-(depth + all));
+        if (g0 == a) depth = 0.;
+        else if (g0 != last) depth -= row_sum64(sum64(tau));
+        if (g0 == last) end = ga * expf(-((float)depth + all));
         float alpha[kPer], w[kPer], next[kPer];   // next: T_{i+1}
         alphas(tau, alpha);
-        float d = depth + dpp<0x111>(incl);
+        float d = (float)depth + dpp<0x111>(incl);
         float T = exp_neg(d);
         float wq = 0.f;
 #pragma unroll
