@@ -415,8 +415,8 @@ extern "C" ogv_status ogv_batch_create(const ogv_scene *scenes, int32_t n, int32
         d.o = sc.origins_dev;
         d.d = sc.dirs_dev;
         d.n = sc.n_rays;
-        d.width = sc.image_width;
-        d.nt = tiled_threads(sc.n_rays, sc.image_width);
+        d.width = tiled_width(sc.n_rays, sc.image_width);
+        d.nt = tiled_threads(sc.n_rays, d.width);
         d.first = b->ray_base[i];
         const size_t tb = d.g.kind == 1 ? tree_lds_bytes(d.g.L, d.g.NR, d.g.S) : 0;
         d.lds = d.g.kind == 1 && tb <= kBatchTreeLds ? 1 : 0;

@@ -411,6 +411,7 @@ RunReader reader_of(const Bufs &b) {
 template <int kGrid, bool kSkip, bool kLds>
 void launch_count(const GridView &g, const float *o, const float *d, int64_t n, const Lattice &lat, const Bufs &b,
                   int width, hipStream_t s) {
+    width = tiled_width(n, width);
     unsigned blocks = (unsigned)((tiled_threads(n, width, b.parts_log2) + kBlock - 1) / kBlock);
     size_t shm = kLds ? lds_bytes(g) : 0;
     const RowMap rows = row_map(n, b.parts_log2, g.L);

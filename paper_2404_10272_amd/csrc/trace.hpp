@@ -15,6 +15,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "geometry.hpp"
@@ -1536,6 +1537,11 @@ __device__ __forceinline__ void expand_block(int64_t *__restrict__ offsets, cons
 }
 
 // ------------------------------------------------------------------ ray order
+
+// The width a call's image is tiled by: a row longer than the call has rays is cut
+// to them (only whole tiles of no ray are left out, of which an image width far
+// beyond the rays would launch any number).
+inline int tiled_width(int64_t n, int width) { return (int)std::min<int64_t>(width, std::max<int64_t>(n, 1)); }
 
 // Threads per image-tiled launch: 8x8-pixel tiles of 64 lanes (one wave);
 // with rays walked in parts, 2^parts_log2 threads a ray.
