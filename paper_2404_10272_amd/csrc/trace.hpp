@@ -35,8 +35,11 @@ constexpr int kBlock = 256;
 //   T(p) = fl(fl(fl(B + fl(p * hs)) - o) * r),   hs = h or -h,
 // which is the plane crossing of the definition bit for bit (a sign moved
 // through a product changes no rounding).  T never decreases along the ray.
-// An axis that does not move has hs = 0, o = -inf, r = 1: every T is +inf,
-// with no test on any step.
+// An axis that does not move has hs = 0, o = -(largest float), r = 1: every T is
+// the largest float, which no parameter of a walk passes, with no test on any step;
+// its `per` is such that a relocation's estimate (below) is sure and keeps the
+// voxel.  (Beside box coordinates of 2^100 and more, which that T would feel, o is
+// -inf and T +inf.)
 struct WalkAxis {
     float B, hs, o, r;
     float per;      // approximate voxels per unit of parameter, for relocation
@@ -59,9 +62,9 @@ __device__ __forceinline__ WalkAxis walk_axis(const float *geom, int lev, int a,
     WalkAxis x;
     x.B = B;
     x.hs = moves ? (d > 0.0f ? h : -h) : 0.0f;
-    x.o = moves ? o : -__builtin_huge_valf();
+    x.o = moves ? o : fabsf(B) < 0x1p100f ? -0x1.fffffep127f : -__builtin_huge_valf();
     x.r = moves ? r : 1.0f;
-    x.per = __builtin_amdgcn_rcpf(x.hs * x.r);
+    x.per = moves ? __builtin_amdgcn_rcpf(x.hs * x.r) : 65535.5f * 0x1p-128f;
     x.flip = moves && d < 0.0f ? -1 : 0;
     return x;
 }
@@ -78,10 +81,11 @@ __device__ __forceinline__ WalkAxis walk_axis(const float *geom, int lev, int a,
 // of at most 2^8 voxels.  Where q is further than `slack` (twice both bounds)
 // from an integer, the estimate is the answer; elsewhere, one time in about
 // a thousand, exact comparisons settle it, as they do for a NaN or infinite
-// q.  Ten instructions an axis, where a binary search over eight voxels takes
+// q.  An axis that does not move has q = 65535.5 at small t and half of it at
+// t = 2^127, which keeps w (walks that go beyond are settled exactly).  Ten instructions an axis, where a binary search over eight voxels takes
 // about thirty.
-__device__ __forceinline__ float relocate_slack(const float *geom, int lev, int R, const float o[3]) {
-    float s = 0.0f;
+__device__ __forceinline__ float relocate_slack(const float *geom, int lev, int R, const float o[3], float tmax) {
+    float s = tmax > 0x1p127f ? __builtin_huge_valf() : 0.0f;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const float B = geom[12 * lev + a], h = geom[12 * lev + 3 + a];
@@ -814,7 +818,7 @@ __device__ __forceinline__ bool cursor_begin(typename CursorOf<kGrid>::type &c, 
     } else if constexpr (kGrid == 2) {
         c.dist = g.dist + (uint64_t)lev * R * R * R;
         c.R = R;
-        c.slack = relocate_slack(g.geom, lev, R, ray.o);
+        c.slack = relocate_slack(g.geom, lev, R, ray.o, lat.tmax);
         c.w0 = w[0];
         c.w1 = w[1];
         c.w2 = w[2];
@@ -823,7 +827,7 @@ __device__ __forceinline__ bool cursor_begin(typename CursorOf<kGrid>::type &c, 
         c.t = tree;
         c.lev = lev;
         c.set_node(tree.root[tree.NR == 1 ? lev : 0]);   // of the level's only root cell, else set by the lookup
-        c.slack = relocate_slack(g.geom, lev, R, ray.o);
+        c.slack = relocate_slack(g.geom, lev, R, ray.o, lat.tmax);
         c.w0 = w[0];
         c.w1 = w[1];
         c.w2 = w[2];

@@ -1,5 +1,5 @@
 """The ray walk's own code compiled for the host: rays walked in parts against
-the same rays walked whole, on the CPU."""
+the same rays walked whole, and relocations of rays with still axes, on the CPU."""
 import ctypes
 import os
 import subprocess
@@ -127,3 +127,32 @@ def test_both_walks_cut_a_one_level_ray_alike(walk, R):
             one, any_level = ([tuple(r) for r in runs_of(walk, g, o, d, near, far, (j, n), single) if r[0] < far]
                               for single in (True, False))
             assert one == any_level, (k, j, n)
+
+
+@pytest.mark.parametrize("still", [[], [0], [2], [0, 1], [1, 2]])
+def test_still_axes_leave_relocations_to_the_estimate(walk, still):
+    """A ray along grid planes settles as many relocations by the estimate as any
+    other: its still axes keep their voxels."""
+    rng = np.random.default_rng(9840)
+    R = 128
+    g = Grid(np.ones((1, 8, 8, 8)), [[-1.5] * 3 + [1.5] * 3])
+    g.geom[0, 3:6] = np.float32(3) / np.float32(R)
+    g.geom[0, 6:9] = np.float32(1) / g.geom[0, 3:6]
+    h = float(g.geom[0, 3])
+    exact = 0
+    for k in range(400):
+        o = rng.uniform(-1.4, 1.4, 3).astype(np.float32)
+        d = rng.uniform(0.2, 1.0, 3).astype(np.float32)
+        d[still] = 0.0
+        w = np.floor((o.astype(np.float64) + 1.5) / h).astype(np.int32) & ~7    # its 8^3 block, entered somewhere
+        p = (w + 8).astype(np.int32)
+        at = np.floor((o.astype(np.float64) + 1.5) / h).astype(np.int32)
+        moving = [a for a in range(3) if a not in still]
+        t = np.float32(min((-1.5 + float(p[a]) * h - float(o[a])) / float(d[a]) for a in moving) * rng.uniform(0.05, 0.95))
+        got = w.copy()
+        got[still] = at[still]
+        exact += walk.relocation(R, _p(g.geom), _p(o), _p(d), _p(got), _p(p), ctypes.c_float(t)) > 0
+        want = np.floor((o + d.astype(np.float64) * float(t) + 1.5) / h).astype(np.int32)
+        want[still] = at[still]
+        assert (np.abs(got - want) <= 0).all() or np.abs((o + d.astype(np.float64) * float(t) + 1.5) / h % 1 - 0.5).max() > 0.4999
+    assert exact <= 8, exact

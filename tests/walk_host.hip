@@ -1,5 +1,5 @@
 // The ray walk of trace.hpp compiled for the host, for tests that need no GPU:
-// a dense grid's rays walked whole and in parts, and the relocation estimate.
+// a dense grid's rays walked whole and in parts, and relocations.
 // Only what the walk itself uses of the device's builtins is given a host form.
 #include <hip/hip_runtime.h>
 
@@ -10,7 +10,8 @@
 #undef __shared__
 #define __shared__ static
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
-#define __fmul_rn(a, b) ((a) * (b))
+static int products;   // of plane crossings computed so far
+#define __fmul_rn(a, b) (++products, (a) * (b))
 #define __fadd_rn(a, b) ((a) + (b))
 #define __fsub_rn(a, b) ((a) - (b))
 #define __fdiv_rn(a, b) ((a) / (b))
@@ -59,12 +60,13 @@ extern "C" int walk_runs(int L, int R, const float *geom, const uint32_t *bits, 
     return runs.n;
 }
 
-// The relocation estimate of one axis (origin o, direction d) of a one-level
-// grid for a ray that steps at t out of a cell of voxels w .. p-1; returns the
-// voxel, and in *sure whether the estimate settles it.
-extern "C" int relocation(int R, const float *geom, int axis, const float *o, float d, int w, int p, float t, int *sure) {
-    const WalkAxis A = walk_axis(geom, 0, axis, o[axis], d, 1.0f / d);
-    const Relocation r = relocate_estimate(A, w, p, A.T(p), t, relocate_slack(geom, 0, R, o));
-    *sure = r.sure;
-    return r.e;
+// Relocation of a ray of a one-level grid that steps at t out of a cell of voxels
+// w[a] .. p[a]-1; returns the products it computed beside the estimates.
+extern "C" int relocation(int R, const float *geom, const float *o, const float *d, int *w, const int *p, float t) {
+    WalkAxis A[3];
+    for (int a = 0; a < 3; ++a) A[a] = walk_axis(geom, 0, a, o[a], d[a], 1.0f / d[a]);
+    const float T[3] = {A[0].T(p[0]), A[1].T(p[1]), A[2].T(p[2])};
+    products = 0;
+    relocate(A[0], A[1], A[2], w[0], w[1], w[2], p[0], p[1], p[2], T[0], T[1], T[2], t, relocate_slack(geom, 0, R, o, 100.0f));
+    return products;
 }
