@@ -28,6 +28,7 @@ namespace ogv {
 namespace {
 
 constexpr int kMaxScenes = 64;
+static_assert(kMaxScenes <= 256, "the expansion keeps a row's scene in a byte");
 
 struct SceneDesc {
     GridView g;

@@ -1231,7 +1231,7 @@ struct Points {
     float tmin, dt;
     const float *tab;
     int n_tab;
-    __device__ __forceinline__ void at(int n, float &a, float &b) const {
+    __device__ __forceinline__ void at(int n, int32_t, float &a, float &b) const {
         if constexpr (kTable) {
             // outputs beside the written ones are looked up too
             n = min(max(n, 0), n_tab - 2);
@@ -1242,6 +1242,21 @@ struct Points {
             a = __fadd_rn(tmin, __fmul_rn(f, dt));
             b = __fadd_rn(tmin, __fmul_rn(f + 1.0f, dt));
         }
+    }
+};
+
+// Points of a chunk of rows that several scenes share: each by its ray's scene.
+struct ScenePoints {
+    const Lattice *lats;
+    const uint8_t *scene;   // [kBlock], in LDS: of each row
+    int64_t r0;             // first row's ray
+    __device__ __forceinline__ void at(int n, int32_t ray, float &a, float &b) const {
+        a = b = 0.0f;
+        if (ray < 0) return;   // a placeholder
+        const Lattice L = lats[scene[ray - r0]];
+        if (!L.cone) Points<false>{L.tmin, L.dt, nullptr, 0}.at(n, ray, a, b);
+        // a growing step with far < near has no table, and its rays no samples
+        else if (L.n_tab > 0) Points<true>{L.tmin, L.dt, L.tab, L.n_tab}.at(n, ray, a, b);
     }
 };
 
@@ -1258,17 +1273,16 @@ struct ChunkOut {
     int2 s0, s1;           // the first two
 };
 
-// Writes the outputs of the part's windows whose rows are `mine`; the others'
-// runs become placeholders.  Entered and left by the whole block.
+// Writes the outputs of the part's windows.  Entered and left by the whole block.
 template <class P>
-__device__ __forceinline__ void expand_windows(ExpandLds &sh, const ChunkOut &ch, int part, bool mine,
+__device__ __forceinline__ void expand_windows(ExpandLds &sh, const ChunkOut &ch, int part,
                                                const RunReader &rd, const P &pts, int32_t *__restrict__ ray_ids,
                                                float *__restrict__ t0, float *__restrict__ t1, bool vec4) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     int nr = ch.nr;
     int32_t ray = ch.ray;
     int2 s0 = ch.s0;
-    if (nr != 0 && (nr == kRunsLost || !mine)) {
+    if (nr == kRunsLost) {
         nr = ch.len > 0 ? 1 : 0;
         s0 = make_int2(0, (int)ch.len);
         ray = -1;
@@ -1364,13 +1378,13 @@ __device__ __forceinline__ void expand_windows(ExpandLds &sh, const ChunkOut &ch
                     auto one = [&](uint32_t j, int32_t &r, float &u, float &v) {
                         const RunBody b = sh.body[max(a - (int)(sa > j) - (int)(sb > j) - (int)(sc > j), 0)];
                         r = b.ray;
-                        pts.at((int)(b.bn + j), u, v);
+                        pts.at((int)(b.bn + j), r, u, v);
                     };
                     one(p, id.x, x0.x, x1.x);
                     one(p + 1, id.y, x0.y, x1.y);
                     one(p + 2, id.z, x0.z, x1.z);
                     id.w = sh.body[a].ray;
-                    pts.at((int)(sh.body[a].bn + p + 3), x0.w, x1.w);
+                    pts.at((int)(sh.body[a].bn + p + 3), id.w, x0.w, x1.w);
                     if (vec4 && p >= lo && p + 3 < hi && (id.x | id.y | id.z | id.w) >= 0) {
                         reinterpret_cast<int4 *>(wi)[k] = id;
                         reinterpret_cast<float4 *>(w0)[k] = x0;
@@ -1487,26 +1501,29 @@ __device__ __forceinline__ void expand_chunk(ExpandLds &sh, const float *table_l
     }
     ch.start = in ? (uint32_t)(off - origin) : 0u;
     ch.len = in ? (uint32_t)(off_next - off) : 0u;
-    auto write = [&](bool mine, const Lattice &L, bool in_lds) {
+    auto write = [&](const Lattice &L, bool in_lds) {
         if (!L.cone)
-            expand_windows(sh, ch, part, mine, rd, Points<false>{L.tmin, L.dt, nullptr, 0}, ray_ids, t0, t1, vec4);
+            expand_windows(sh, ch, part, rd, Points<false>{L.tmin, L.dt, nullptr, 0}, ray_ids, t0, t1, vec4);
         else if (in_lds)
-            expand_windows(sh, ch, part, mine, rd, Points<true>{L.tmin, L.dt, table_lds, L.n_tab}, ray_ids, t0, t1,
-                           vec4);
+            expand_windows(sh, ch, part, rd, Points<true>{L.tmin, L.dt, table_lds, L.n_tab}, ray_ids, t0, t1, vec4);
         else
-            expand_windows(sh, ch, part, mine, rd, Points<true>{L.tmin, L.dt, L.tab, L.n_tab}, ray_ids, t0, t1, vec4);
+            expand_windows(sh, ch, part, rd, Points<true>{L.tmin, L.dt, L.tab, L.n_tab}, ray_ids, t0, t1, vec4);
     };
     if constexpr (Lats::kMulti) {
-        // scene by scene: nearly every chunk lies in one
-        const int64_t r1 = min(r0 + kBlock, n_rays);
-        for (int sc = lats.scene_of(r0); sc < lats.n && lats.first[sc] < r1; ++sc) {
-            const Lattice L = lats.lats[sc];
-            // a growing step with far < near has no table to look points up in, and its rays no samples
-            if (L.cone && L.n_tab == 0) continue;
-            write(r >= lats.first[sc] && r < lats.first[sc + 1], L, false);
+        // nearly every chunk lies in one scene; scene by scene, a chunk of many
+        // small ones would be written once for each (64 scenes of 4 rays: 482 us)
+        __shared__ uint8_t scene[kBlock];
+        int sc = lats.scene_of(r0);
+        if (lats.first[sc + 1] >= min(r0 + kBlock, n_rays)) {
+            write(lats.lats[sc], false);
+        } else {
+            while (lats.first[sc + 1] <= rc) ++sc;
+            scene[threadIdx.x] = (uint8_t)sc;
+            __syncthreads();
+            expand_windows(sh, ch, part, rd, ScenePoints{lats.lats, scene, r0}, ray_ids, t0, t1, vec4);
         }
     } else {
-        write(true, lats.lat, lats.lat.n_tab <= kTableLds);
+        write(lats.lat, lats.lat.n_tab <= kTableLds);
     }
 }
 
