@@ -701,7 +701,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))
 
     const uint64_t some = __ballot(chunks > 0);
     const int rays = __popcll(some), slot = __popcll(some & ((1ull << lane) - 1));
-    int32_t last = chunks;   // inclusive scan over the first 16 lanes
+    int32_t last = chunks;   // inclusive scan over the first kWaveRays lanes
 #pragma unroll
     for (int off = 1; off < kWaveRays; off <<= 1) {
         const int32_t y = __shfl_up(last, off, 64);

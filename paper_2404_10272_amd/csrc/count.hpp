@@ -64,8 +64,10 @@ __device__ __forceinline__ void add_chunk_sums(int64_t ray, int32_t n, int64_t *
 // k*kScanTile .. (k+1)*kScanTile-1.
 //
 // Bound by VALU issue while the chip is full: an 800x800 view of a 128^3 grid
-// issues 56.6 M wave instructions walking the tree (87.0 M on the bitfield),
-// 92 (141) us at one per four clocks and SIMD, of 113-128 (133) us measured,
+// issues 56.8 M wave instructions walking the tree (87.1 M on the bitfield),
+// 92 (142) us at one per four clocks and SIMD at 2.4 GHz, and takes 113-130
+// (133-140) us: the true rate is a little above one per four clocks, as the
+// bitfield's walk shows, and the tree's walk waits for a quarter of its time,
 // with 85% of the lanes active.  The steps compute all three axes' crossings
 // and select instead of branching per axis; with branches the same walks took
 // 142-156 (166-172) us at 64% of the lanes, the four-cascade one 310 us
